@@ -16,25 +16,25 @@
 // workgroup) deals the attention's work items to workgroup ids so that the
 // CUs get even shares: a query block late in the window sees many more key
 // tiles than an early one.  Then one workgroup per (64 queries, head, key
-// split); each of its 4 waves owns 16 queries.  Key tiles that none of its
-// queries can see are skipped, and a split none of them sees ends the
-// workgroup before its queries are rotated.  Per 32-key tile:
-//   - the workgroup stages the rotated keys (bf16, [key][d]) and the values
-//     transposed ([d][key]) in LDS;
-//   - a wave forms S^T = K Q^T with v_mfma_f32_16x16x32_bf16 (its rotated
+// split), 2 query halves by 2 key halves of waves.  The workgroup lists the
+// key tiles that some query of it can see; a split none of them sees ends
+// the workgroup before its queries are rotated.  Per listed tile:
+//   - rotated keys and values go from memory straight into LDS ([key][d],
+//     rows swizzled), a stage of two tiles ahead of their use;
+//   - a wave forms S^T = K Q^T with v_mfma_f32_32x32x16_bf16 (its 32 rotated
 //     queries are the B operand, held in registers), so a lane holds one
-//     query's scores for 8 keys;
+//     query's scores for 16 keys;
 //   - online softmax in fp32: base-2 hardware exponentials of
 //     score * (scale log2 e) - running maximum as one fused multiply-add
 //     (weights below 2^-126 of the largest may flush to 0), the per-score
-//     position test only on tiles that straddle a query of the wave, and
-//     row swaps across the lane groups of a query;
-//   - the weights rounded to bf16 as the B operand of O^T += V^T P^T; the 8
-//     keys a lane holds are the reduction indices of its lane group, and V^T
-//     is read from LDS in the same key order.
+//     position test only on tiles that straddle a query of the wave;
+//   - the weights rounded to bf16 as the B operand of O^T += V^T P^T; the
+//     keys a lane holds are the reduction indices of its lane half, and V^T
+//     comes out of LDS in the same key order through transposing reads.
 // Rotations are fp32 IEEE operations rounded to bf16, as a bf16 model holds
 // its rotated operands.
 #include <climits>
+#include <type_traits>
 
 #include "device.h"
 #include "attention.h"
@@ -45,30 +45,21 @@ namespace w4a8 {
 namespace {
 
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
-typedef float f32x4_t __attribute__((ext_vector_type(4)));
+typedef float f32x16_t __attribute__((ext_vector_type(16)));
+typedef short v4s_t __attribute__((ext_vector_type(4)));
 
 constexpr int kD = 128;          // head dimension
 constexpr int kHalf = kD / 2;    // rotate-half pairing (d, d + 64)
-constexpr int kQPerWave = 16;
-constexpr int kAttnWaves = 4;
-constexpr int kQPerBlock = kQPerWave * kAttnWaves;
+constexpr int kQPerWave = 32;
+constexpr int kAttnWaves = 4;    // two query halves by two key halves
+constexpr int kQPerBlock = 2 * kQPerWave;
 constexpr int kKeys = 32;        // keys per tile
-// LDS row pitches (bf16 elements), padded against bank conflicts: the key
-// rows' 16-byte reads by 16 lanes (one per key) and the transposed value
-// tile's dword writes (two keys of one d) and 8-byte reads
-constexpr int kKPitch = kD + 8;
-constexpr int kVtPitch = kKeys + 4;
 
 __device__ __forceinline__ bf16x8_t as_bf16x8(uint4 u) { return __builtin_bit_cast(bf16x8_t, u); }
 
-// Reductions over the lane pairs (l, l ^ 16) and (l, l ^ 32) with the gfx950
-// row swaps (no LDS round trip): each swap hands a lane its partner's value
-// in one of the two results and its own in the other.  Scores are never NaN.
-__device__ __forceinline__ float max_xor16(float x) {
-  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  const float a = __uint_as_float(r[0]), b = __uint_as_float(r[1]);
-  return a > b ? a : b;
-}
+// Maximum over the lane pair (l, l ^ 32) with the gfx950 row swap (no LDS
+// round trip): the swap hands a lane its partner's value in one of the two
+// results and its own in the other.  Scores are never NaN.
 __device__ __forceinline__ float max_xor32(float x) {
   const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
   const float a = __uint_as_float(r[0]), b = __uint_as_float(r[1]);
@@ -118,39 +109,49 @@ __device__ void build_schedule(const AttnArgs& a) {
   const int tid = threadIdx.x;
   const int X = (a.Nq + kQPerBlock - 1) / kQPerBlock, ntiles = (a.Nk + kKeys - 1) / kKeys;
   const int S = a.S, n = X * S, H = a.H;
-  // each block's largest query position and each tile's smallest key
-  // position: every thread sweeps the position arrays with independent
-  // loads and folds them into LDS with atomics
-  for (int x = tid; x < X; x += 256) s_qmax[x] = INT_MIN;
-  for (int t = tid; t < ntiles; t += 256) s_tmin[t] = INT_MAX;
-  __syncthreads();
-  // both position arrays swept together, so that every thread's loads of
-  // both go out before any of its atomics
-  constexpr int kBatch = 16;  // loads in flight per array and thread
-  const int span = max(a.Nq, a.Nk);
-  for (int i0 = tid; i0 < span; i0 += 256 * kBatch) {
-    int vq[kBatch], vk[kBatch];
+  // Each block's largest query position and each tile's smallest key
+  // position: 16 lanes fold a block's 64 and 8 lanes a tile's 32 (four each)
+  // with shuffles.  (One LDS atomic per position took 5.6 us of the 9 us
+  // that this kernel took on the 4 x 4 x 192 window.)
+  auto load4 = [](const int* p, int i, int n, int none) {
+    return make_int4(i < n ? p[i] : none, i + 1 < n ? p[i + 1] : none, i + 2 < n ? p[i + 2] : none,
+                     i + 3 < n ? p[i + 3] : none);
+  };
+  const int span = max(X * 16, ntiles * 8);
+  for (int i0 = tid; i0 < span; i0 += 256 * 4) {
+    int4 q4[4], k4[4];  // every load of a batch goes out first
 #pragma unroll
-    for (int b = 0; b < kBatch; ++b) {
-      const int i = i0 + 256 * b;
-      vq[b] = i < a.Nq ? a.pos_q[i] : INT_MIN;
-      vk[b] = i < a.Nk ? a.pos_k[i] : INT_MAX;
+    for (int b = 0; b < 4; ++b) {
+      const int i = (i0 + 256 * b) * 4;
+      q4[b] = load4(a.pos_q, i, a.Nq, INT_MIN);
+      k4[b] = load4(a.pos_k, i, a.Nk, INT_MAX);
     }
 #pragma unroll
-    for (int b = 0; b < kBatch; ++b) {
+    for (int b = 0; b < 4; ++b) {
       const int i = i0 + 256 * b;
-      if (i < a.Nq) atomicMax(&s_qmax[i / kQPerBlock], vq[b]);
-      if (i < a.Nk) atomicMin(&s_tmin[i / kKeys], vk[b]);
+      int mx = max(max(q4[b].x, q4[b].y), max(q4[b].z, q4[b].w)), mn = min(min(k4[b].x, k4[b].y), min(k4[b].z, k4[b].w));
+#pragma unroll
+      for (int off = 8; off >= 1; off >>= 1) mx = max(mx, __shfl_xor(mx, off, 64));
+#pragma unroll
+      for (int off = 4; off >= 1; off >>= 1) mn = min(mn, __shfl_xor(mn, off, 64));
+      if ((tid & 15) == 0 && i / 16 < X) s_qmax[i / 16] = mx;
+      if ((tid & 7) == 0 && i / 8 < ntiles) s_tmin[i / 8] = mn;
     }
   }
-  for (int c = tid; c < n; c += 256) s_vis[c] = 0;
   __syncthreads();
-  // visible tiles of each (block, split) class, one (class, tile) pair per
-  // thread and step (the counter a lane adds to depends on its index)
+  // visible tiles of each (block, split) class, 8 lanes to a class
   const int tps = a.tiles_per_split;
-  for (int i = tid; i < n * tps; i += 256) {
-    const int c = i / tps, t = (c % S) * tps + (i - c * tps);
-    if (t < ntiles && s_tmin[t] <= s_qmax[c / S]) atomicAdd(&s_vis[c], 1);
+  for (int i0 = 0; i0 < n * 8; i0 += 256) {
+    const int c = (i0 + tid) >> 3;
+    int cnt = 0;
+    if (c < n) {
+      const int qm = s_qmax[c / S], t0 = (c % S) * tps, t1 = min(t0 + tps, ntiles);
+#pragma unroll 4
+      for (int t = t0 + (tid & 7); t < t1; t += 8) cnt += s_tmin[t] <= qm ? 1 : 0;
+    }
+#pragma unroll
+    for (int off = 4; off >= 1; off >>= 1) cnt += __shfl_xor(cnt, off, 64);
+    if ((tid & 7) == 0 && c < n) s_vis[c] = cnt;
   }
   __syncthreads();
   // a block whose keys only one split sees: that split writes the output
@@ -248,28 +249,59 @@ __global__ __launch_bounds__(256) void rotate_keys(const AttnArgs a) {
     }
 }
 
-// Per-tile minimum key positions kept for the skip test (tiles beyond this
-// count are never skipped).
+// Key tiles of a split whose visible ones are listed (longer splits visit
+// every tile and test every score).
 constexpr int kMaxSkipTiles = 512;
 
-// The occupancy hint (4 workgroups, i.e. 4 waves per SIMD) holds the kernel
-// to 128 registers (it needs 110, without spills); LDS (39.3 KiB per
-// workgroup) also fits 4.
-__global__ __launch_bounds__(kAttnWaves * 64, 4) void stream_attention(const AttnArgs a) {
-  // two stages of the key / value tile: the next visible tile is staged
-  // while the current one is computed
-  __shared__ __align__(16) uint16_t l_k[2][kKeys * kKPitch];     // rotated keys [key][d]
-  __shared__ __align__(16) uint16_t l_vt[2][kD * kVtPitch];      // values transposed [d][key]
-  __shared__ int l_pos[2][kKeys];
-  __shared__ int l_tmin[kMaxSkipTiles];
-  __shared__ int l_tmax[kMaxSkipTiles];
-  __shared__ int l_qmax[kAttnWaves];
+constexpr int kStageTiles = 2;                     // key tiles per LDS stage, one per key group of waves
+constexpr int kTileBytes = kKeys * kD * 2;         // one tile of keys or values, 8 KiB
+constexpr int kStageKV = kStageTiles * kTileBytes; // a stage's keys (or values)
+constexpr int kPosBytes = 256;                     // a wave's copy of its tile's key positions (128 bytes; one load fills 256)
+// LDS: the keys of two stages, their values, their key positions, then the
+// list of visible tiles; the halves' merge reuses the keys and values.
+constexpr int kLdsV = 2 * kStageKV, kLdsPos = 2 * kLdsV, kLdsList = kLdsPos + 2 * kAttnWaves * kPosBytes;
+constexpr int kLdsAttn = kLdsList + kMaxSkipTiles * 2;
+static_assert(kMaxSkipTiles <= 512, "a list entry holds 9 bits of tile number");
+
+// One workgroup per (64 queries, head, key split), 4 waves: a wave owns the
+// 32 queries of half qh and every second visible key tile (kh); the two key
+// halves meet in LDS at the end.  What bounds it is feeding the operands
+// (the L2-to-LDS fill reaches ~60 GB/s per CU beside matrix instructions;
+// LDS serves 128 bytes a clock) and the vector instructions of the softmax,
+// which take 4 cycles each while a matrix instruction runs.  So a key or
+// value fragment read from LDS feeds 32 queries, the tiles go from memory
+// straight into the LDS stage (no registers), and the softmax rescales
+// only where a maximum moves (below).  The 4 x 4 x 192 window with 32 heads took
+// 65.7 us with 16 queries a wave and values transposed through registers,
+// 46 us so.  (Two heads of a kv head per workgroup of 8 waves halve the
+// fill and took 43 us: one workgroup per CU, whose waves all wait at once.)
+// Rows are swizzled by the fetching lanes:
+//   keys    16-byte chunk c of key j at c ^ (j & 15): the 16 keys that an
+//           operand read touches at once lie on 16 distinct chunks;
+//   values  chunk c of key j at c ^ 4 (j & 3): the transposed read takes 4
+//           chunks of 4 consecutive keys at once.
+// The values' operand (d by key) comes out of the row-major tile with the
+// transposing LDS read.  The scores of the next stage are formed under this
+// stage's softmax, so the keys run one stage ahead of the values.
+__global__ __launch_bounds__(kAttnWaves * 64, 2) void stream_attention(const AttnArgs a) {
+  extern __shared__ __align__(16) uint8_t lds[];
+  __shared__ int l_qmax[2], l_qmin[2];
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int qh = wave & 1, kh = wave >> 1;  // query half, key half
   int xb = blockIdx.x, h = blockIdx.y, split = blockIdx.z;  // this workgroup's item
   if (a.sched) {  // a 1-D grid dealt by the schedule
-    const int code = a.sched[blockIdx.x], c = code / a.H;
+    // Ids go round robin over the 8 XCDs: within a run of H ids (the heads
+    // of one class) id t takes the head of id (t % 8) (H / 8) + t / 8, so
+    // that an XCD works on neighbouring heads, whose keys its L2 then holds
+    // once.
+    int id = blockIdx.x;
+    if ((a.H & 7) == 0) {
+      const int t = id % a.H;
+      id += (t & 7) * (a.H >> 3) + (t >> 3) - t;
+    }
+    const int code = a.sched[id], c = code / a.H;
     h = code % a.H;
     xb = c / a.S;
     split = c % a.S;
@@ -277,242 +309,420 @@ __global__ __launch_bounds__(kAttnWaves * 64, 4) void stream_attention(const Att
   // this split alone sees keys of the block: it writes the output itself
   const bool final_out = a.S == 1 || (a.sched && a.solo[xb] == split);
   const int hk = h / (a.H / a.Hkv);
-  const int r16 = lane & 15, g = lane >> 4;
+  const int l32 = lane & 31, hi = lane >> 5;
   const int P = a.n_pos;
   auto clamp_pos = [&](int p) { return p < 0 ? 0 : (p >= P ? P - 1 : p); };  // table reads stay in bounds
 
   // ---- this lane's query: rotated, as the B operand of S^T = K Q^T
-  // (lane: query r16, d chunk 32 i + 8 g for MFMA i; chunks i and i + 2 are
+  // (lane: query l32, d = 16 i + 8 hi .. for MFMA i; chunks i and i + 4 are
   // a rotate-half pair)
-  const int qi = xb * kQPerBlock + wave * kQPerWave + r16;
+  const int qi = xb * kQPerBlock + qh * kQPerWave + l32;
   const bool q_ok = qi < a.Nq;
+  // Everything that the item alone decides is requested at once: the query's
+  // position, the split's first tile bounds, the query.
   const int pq = q_ok ? a.pos_q[qi] : INT_MIN;
+  const int ntiles_all = (a.Nk + kKeys - 1) / kKeys;
+  const int t_begin = split * a.tiles_per_split;
+  const int t_end = min(ntiles_all, t_begin + a.tiles_per_split);
+  const int2 bounds0 = a.tile_bounds[min(t_begin + lane, ntiles_all - 1)];
   // Rows past Nq and keys past Nk are out-of-range buffer offsets, which
-  // read zeros (selects of a loaded value against a zero vector had put the
-  // zero in scratch memory, on the loop's critical path).
+  // read zeros.
   const __amdgpu_buffer_rsrc_t qres = make_rsrc(a.q + (size_t)h * a.Nq * kD, (uint32_t)((size_t)a.Nq * kD * 2));
-  uint4 qraw[2][2];  // chunks (32 i + 8 g, + 64), rotated once the block is known to see a key
+  uint4 qraw[4][2];  // chunks (16 i + 8 hi, + 64), rotated once the block is known to see a key
   {
     const uint32_t qoff = q_ok ? (uint32_t)(qi * kD * 2) : kOOB;
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const int d = 32 * i + 8 * g;  // < 64
+    for (int i = 0; i < 4; ++i) {
+      const int d = 16 * i + 8 * hi;  // < 64
       qraw[i][0] = buf_load16(qres, qoff == kOOB ? kOOB : qoff + d * 2);
       qraw[i][1] = buf_load16(qres, qoff == kOOB ? kOOB : qoff + (d + kHalf) * 2);
     }
   }
 
-  // ---- this workgroup's key tiles (its split of the key range) and the
-  // skip test: a tile none of its queries can see (every key position above
-  // the largest query position) is not staged
-  const int ntiles_all = (a.Nk + kKeys - 1) / kKeys;
-  const int t_begin = split * a.tiles_per_split;
-  const int ntiles = min(ntiles_all, t_begin + a.tiles_per_split);  // one past the last tile
-  const bool skipping = ntiles - t_begin <= kMaxSkipTiles;
-  int wave_qmin;  // the wave's smallest query position (INT_MAX when it has no query)
-  {
-    int qm = pq, qn = q_ok ? pq : INT_MAX;
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-      qm = max(qm, __shfl_xor(qm, off, 64));
-      qn = min(qn, __shfl_xor(qn, off, 64));
-    }
-    if (lane == 0) l_qmax[wave] = qm;
-    wave_qmin = __builtin_amdgcn_readfirstlane(qn);
-    // the split's tile bounds, one tile per thread
-    if (skipping)
-      for (int t = t_begin + tid; t < ntiles; t += kAttnWaves * 64) {
-        const int2 bd = a.tile_bounds[t];
-        l_tmin[t - t_begin] = bd.x;
-        l_tmax[t - t_begin] = bd.y;
-      }
-  }
-  __syncthreads();
-  int wg_qmax = l_qmax[0];
-#pragma unroll
-  for (int w = 1; w < kAttnWaves; ++w) wg_qmax = max(wg_qmax, l_qmax[w]);
-  auto next_visible = [&](int t) {
-    if (skipping)
-      while (t < ntiles && l_tmin[t - t_begin] > wg_qmax) ++t;
-    return t;
-  };
-  int cur = next_visible(t_begin);
-  if (a.S > 1 && cur >= ntiles) {
-    // no query of the block sees a key of this split: an empty partial
-    // (the merge reads only its maximum)
-    if (q_ok && g == 0)
-      *reinterpret_cast<float2*>(a.part_ml + (((size_t)split * a.H + h) * a.Nq + qi) * 2) = make_float2(-INFINITY, 0.0f);
-    return;
-  }
-
-  bf16x8_t qf[4];
+  // the rotary table row of the query (requested before the list is made)
+  float4 rc[4][2], rs[4][2];
   {
     const int pc = clamp_pos(q_ok ? pq : 0);
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const int d = 32 * i + 8 * g;
-      uint4 lo, hi;
-      rotate_chunks(qraw[i][0], qraw[i][1], a.rope_cos + (size_t)pc * kHalf + d, a.rope_sin + (size_t)pc * kHalf + d,
-                    lo, hi);
-      qf[i] = as_bf16x8(lo);
-      qf[i + 2] = as_bf16x8(hi);
-    }
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        rc[i][u] = *reinterpret_cast<const float4*>(a.rope_cos + (size_t)pc * kHalf + 16 * i + 8 * hi + 4 * u);
+        rs[i][u] = *reinterpret_cast<const float4*>(a.rope_sin + (size_t)pc * kHalf + 16 * i + 8 * hi + 4 * u);
+      }
   }
 
-  f32x4_t acc[kD / 16];
+  // ---- this workgroup's key tiles (its split of the key range): the list
+  // of those that some query of the block sees (a tile whose smallest key
+  // position lies above the largest query position is left out); bits 0-8
+  // the tile within the split, bit 9 + q: every key of it is seen by every
+  // query of half q
+  const bool listed = t_end - t_begin <= kMaxSkipTiles;
+  uint16_t* list = reinterpret_cast<uint16_t*>(lds + kLdsList);
+  {
+    int qm = pq, qn = q_ok ? pq : INT_MAX;
 #pragma unroll
-  for (int t = 0; t < kD / 16; ++t) acc[t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-  float m = -INFINITY, lsum = 0.0f;
-  const float sl2 = a.scale_log2e;
-
-  const __amdgpu_buffer_rsrc_t kres =
-      make_rsrc(a.k_rot + (size_t)hk * a.Nk * kD, (uint32_t)((size_t)a.Nk * kD * 2));
-  const __amdgpu_buffer_rsrc_t vres = make_rsrc(a.v + (size_t)hk * a.Nk * kD, (uint32_t)((size_t)a.Nk * kD * 2));
-  // staging: for the keys, thread tid handles key tid / 8 of the tile and
-  // the pair of 8-element chunks (8 c, 64 + 8 c), c = tid % 8; for the
-  // values, keys 2 kp and 2 kp + 1 (kp = tid % 16) and d chunk tid / 16, so
-  // that each transposed store is one dword.  The global loads of the next
-  // tile are issued before the current tile's compute.
-  const int sj = tid >> 3, sc = tid & 7;
-  const int vkp = tid & 15, vc = tid >> 4;
-  uint4 gk0, gk1, gv0, gv1;
-  int gpj;
-  auto load_tile = [&](int t) {
-    const int j = t * kKeys + sj;
-    const bool ok = j < a.Nk;
-    const int jv0 = t * kKeys + 2 * vkp, jv1 = jv0 + 1;
-    gpj = ok ? a.pos_k[j] : INT_MAX;
-    const uint32_t ko = ok ? (uint32_t)((j * kD + 8 * sc) * 2) : kOOB;
-    gk0 = buf_load16(kres, ko);
-    gk1 = buf_load16(kres, ko == kOOB ? kOOB : ko + kHalf * 2);
-    gv0 = buf_load16(vres, jv0 < a.Nk ? (uint32_t)((jv0 * kD + 8 * vc) * 2) : kOOB);
-    gv1 = buf_load16(vres, jv1 < a.Nk ? (uint32_t)((jv1 * kD + 8 * vc) * 2) : kOOB);
-  };
-  auto store_tile = [&](int b) {
-    *reinterpret_cast<uint4*>(&l_k[b][sj * kKPitch + 8 * sc]) = gk0;
-    *reinterpret_cast<uint4*>(&l_k[b][sj * kKPitch + kHalf + 8 * sc]) = gk1;
-    // row d of the transposed tile gets (v[2 kp][d], v[2 kp + 1][d]) as one dword
-    const uint32_t w0[4] = {gv0.x, gv0.y, gv0.z, gv0.w}, w1[4] = {gv1.x, gv1.y, gv1.z, gv1.w};
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      uint32_t* r0 = reinterpret_cast<uint32_t*>(&l_vt[b][(8 * vc + 2 * e) * kVtPitch + 2 * vkp]);
-      uint32_t* r1 = reinterpret_cast<uint32_t*>(&l_vt[b][(8 * vc + 2 * e + 1) * kVtPitch + 2 * vkp]);
-      *r0 = __builtin_amdgcn_perm(w1[e], w0[e], 0x05040100u);  // low halves: d = 8 vc + 2 e
-      *r1 = __builtin_amdgcn_perm(w1[e], w0[e], 0x07060302u);  // high halves: d + 1
+    for (int off = 16; off >= 1; off >>= 1) {
+      qm = max(qm, __shfl_xor(qm, off, 64));
+      qn = min(qn, __shfl_xor(qn, off, 64));
     }
-    if (sc == 0) l_pos[b][sj] = gpj;
+    if (lane == 0 && kh == 0) {
+      l_qmax[qh] = qm;
+      l_qmin[qh] = qn;  // INT_MAX when the half has no query
+    }
+  }
+  lds_barrier();
+  const int wg_qmax = max(l_qmax[0], l_qmax[1]), qmin0 = l_qmin[0], qmin1 = l_qmin[1];
+  int n_vis = t_end - t_begin;
+  if (listed) {
+    n_vis = 0;
+    for (int t0 = t_begin; t0 < t_end; t0 += 64) {  // every wave counts; each fourth batch is one wave's to write
+      const int t = t0 + lane;
+      const int2 bd = t0 == t_begin ? bounds0 : a.tile_bounds[min(t, ntiles_all - 1)];
+      const bool vis = t < t_end && bd.x <= wg_qmax;
+      const uint64_t m = __ballot(vis);
+      if (vis && wave == ((t0 - t_begin) >> 6) % kAttnWaves)
+        list[n_vis + __popcll(m & ((1ull << lane) - 1))] =
+            (uint16_t)((t - t_begin) | (bd.y <= qmin0 ? 512 : 0) | (bd.y <= qmin1 ? 1024 : 0));
+      n_vis += (int)__popcll(m);
+    }
+    n_vis = __builtin_amdgcn_readfirstlane(n_vis);
+  }
+  if (a.S > 1 && n_vis == 0) {
+    // no query of the block sees a key of this split: an empty partial
+    // (the merge reads only its maximum)
+    if (q_ok && hi == 0 && kh == 0)
+      *reinterpret_cast<float2*>(a.part_ml + (((size_t)split * a.H + h) * a.Nq + qi) * 2) = make_float2(-INFINITY, 0.0f);
+    return;
+  }
+  lds_barrier();  // the list
+
+  // ---- staging.  A stage takes the next two listed tiles, kh = 0 and 1 of
+  // them computed by the waves of that key half, and the waves of a key half
+  // fetch its tile: kRows rows each of the keys and of the values, 4 rows
+  // (1 KiB of LDS) per instruction: lane l is row l / 16's chunk l % 16 of
+  // LDS.
+  constexpr int kRows = kKeys / 2, kLoads = kRows / 4;
+  static_assert(kLoads == 4, "a stage deals its loads one to a slot");
+  const uint32_t lds_base = (uint32_t)(uintptr_t)lds;
+  const u32x4 k_res = make_rsrc_words(a.k_rot + (size_t)hk * a.Nk * kD, (uint32_t)((size_t)a.Nk * kD * 2));
+  const u32x4 v_res = make_rsrc_words(a.v + (size_t)hk * a.Nk * kD, (uint32_t)((size_t)a.Nk * kD * 2));
+  const int r4 = lane >> 4, c16 = lane & 15;
+  const int row0 = kRows * qh;  // first row of the tile that this wave fetches
+  uint32_t k_voff[kLoads];
+#pragma unroll
+  for (int n = 0; n < kLoads; ++n) {
+    const int row = row0 + 4 * n + r4;
+    k_voff[n] = (uint32_t)(row * 256 + ((c16 ^ (row & 15)) << 4));
+  }
+  const uint32_t v_voff = (uint32_t)((row0 + r4) * 256 + ((c16 ^ (4 * r4)) << 4));
+  // The wave's tile of the stage of visible tiles i, i + 1, as listed (a
+  // value every lane holds; made scalar where it is used, a stage later, so
+  // that nothing waits for the LDS read).
+  const int last_entry = max(min(n_vis, kMaxSkipTiles) - 1, 0);
+  auto tile_at = [&](int i) {
+    const int e = list[min(i + kh, last_entry)];  // read in any case: no branch
+    return listed ? e : i + kh;
+  };
+  auto scalar = [](int e) { return (int)__builtin_amdgcn_readfirstlane(e); };
+  auto tile_of = [&](int e) { return t_begin + (listed ? e & 511 : e); };
+  const int full_bit = listed ? 512 << qh : 0;
+  const u32x4 pos_res = make_rsrc_words(a.pos_k, (uint32_t)(a.Nk * 4));
+  // Byte offset of the tile's rows in the head's keys and values.  Rows past
+  // Nk lie past the buffers and read zeros; so do all rows of a tile past
+  // the last visible one, without traffic.
+  auto tile_off = [&](int i, int e) { return i + kh < n_vis ? (uint32_t)(tile_of(e) * kTileBytes) : kOOB; };
+  const uint32_t my_rows = lds_base + (uint32_t)(kh * kTileBytes + row0 * 256);
+  auto issue_keys = [&](int b, int n, uint32_t off) {
+    lds_dma16(k_res, my_rows + (uint32_t)(b * kStageKV + n * 1024), k_voff[n] + off, 0);
+  };
+  auto issue_values = [&](int b, int n, uint32_t off) {
+    lds_dma16(v_res, my_rows + (uint32_t)(kLdsV + b * kStageKV + n * 1024), v_voff + n * 1024 + off, 0);
+  };
+  auto issue_pos = [&](int b, uint32_t off) {
+    lds_dma4(pos_res, lds_base + (uint32_t)(kLdsPos + (kAttnWaves * b + wave) * kPosBytes),
+             hi == 0 ? (off == kOOB ? kOOB : off / (kTileBytes / (kKeys * 4))) + l32 * 4 : kOOB, 0);
   };
 
-  auto compute_tile = [&](int b, int t) {
-    // ---- S^T for keys 16 u + (4 g + r), u = 0, 1: lane holds query r16
-    // (raw scores; the scale is applied inside the exponent)
-    float s[2][4];
-    // the position test per score only where some key of the tile lies
-    // beyond some query of the wave
-    const bool full = skipping && l_tmax[t - t_begin] <= wave_qmin;
+  int cur = scalar(tile_at(0)), nxt = scalar(tile_at(kStageTiles)), ahead = tile_at(2 * kStageTiles);
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      f32x4_t c = {0.f, 0.f, 0.f, 0.f};
+  for (int n = 0; n < kLoads; ++n) issue_keys(0, n, tile_off(0, cur));
+
+  bf16x8_t qf[8];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const bf16x8_t kf = as_bf16x8(*reinterpret_cast<const uint4*>(&l_k[b][(16 * u + r16) * kKPitch + 32 * i + 8 * g]));
-        c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf, qf[i], c, 0, 0, 0);
-      }
+  for (int i = 0; i < 4; ++i) {
+    const float cs[8] = {rc[i][0].x, rc[i][0].y, rc[i][0].z, rc[i][0].w, rc[i][1].x, rc[i][1].y, rc[i][1].z, rc[i][1].w};
+    const float sn[8] = {rs[i][0].x, rs[i][0].y, rs[i][0].z, rs[i][0].w, rs[i][1].x, rs[i][1].y, rs[i][1].z, rs[i][1].w};
+    uint4 lo, hi4;
+    rotate_chunks(qraw[i][0], qraw[i][1], cs, sn, lo, hi4);
+    qf[i] = as_bf16x8(lo);
+    qf[i + 4] = as_bf16x8(hi4);
+  }
+
+  f32x16_t acc[kD / 32];
 #pragma unroll
-      for (int r = 0; r < 4; ++r) s[u][r] = c[r];
-    }
-    if (!full) {
+  for (int t = 0; t < kD / 32; ++t)
 #pragma unroll
-      for (int u = 0; u < 2; ++u)
+    for (int r = 0; r < 16; ++r) acc[t][r] = 0.0f;
+  float m = -INFINITY, tmax = -INFINITY;
+  float ls[4] = {0.0f, 0.0f, 0.0f, 0.0f};  // the weights' total, in four chains
+  // (in a vector register: a scalar operand halves the rate of an fma)
+  float sl2 = a.scale_log2e;
+  asm volatile("" : "+v"(sl2));
+
+  // LDS read addresses within a stage: key l32's chunks 2 i + hi; the
+  // transposed value read of (32 t, 16 j + 8 u): lane k of a 16-lane group
+  // addresses row k / 4 of its four keys (16 j + 8 u + 4 hi + ..) and d
+  // chunk k % 4 of its sixteen d (32 t + 16 (group & 1) + ..), and receives
+  // the four keys of d = 32 t + l32.
+  uint32_t k_rd[4];  // MFMAs i and i + 4 are 8 chunks apart
+#pragma unroll
+  for (int i = 0; i < 4; ++i) k_rd[i] = (uint32_t)(kh * kTileBytes + l32 * 256 + (((2 * i + hi) ^ (l32 & 15)) << 4));
+  const int vr = (lane & 15) >> 2;                                    // key row of the four
+  const int vch = 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1);          // 16-byte chunk within 32 t's four
+  __attribute__((address_space(3))) uint8_t* v_rd[kD / 32];
+#pragma unroll
+  for (int t = 0; t < kD / 32; ++t)
+    v_rd[t] = (__attribute__((address_space(3))) uint8_t*)lds + kLdsV + kh * kTileBytes + (4 * hi + vr) * 256 +
+              ((4 * (t ^ vr) + vch) << 4) + 8 * (lane & 1);
+
+  // Fragment i of the keys of stage b (a constant: the immediate offset)
+  auto key_frag = [&](int b, int i) {
+    return as_bf16x8(*reinterpret_cast<const uint4*>(lds + (i < 4 ? k_rd[i & 3] : k_rd[i & 3] ^ 128u) + b * kStageKV));
+  };
+  // Stage b holds visible tiles i, i + 1, whose scores are in s: score 4 q +
+  // r is key 8 q + 4 hi + r of the wave's tile, raw (the scale is applied
+  // inside the exponent).  Unless it is the last, the next stage's scores
+  // are formed into sn.  One barrier per stage: the wait and the barrier
+  // publish this stage's values and the next stage's keys (every wave's
+  // share has landed) and say that the last stage's values and this stage's
+  // keys are no longer read, so their refills go out under this stage's
+  // compute.
+  // The waves pass their phases together, so each wave's own matrix
+  // instructions are dealt out between its vector instructions (slots kept
+  // apart by scheduling barriers): the next scores' and the first half of
+  // the values' under the exponentials, the rest under the next maximum.
+  // In one block each the two units took turns: 43 % and 24 % busy, 1470
+  // cycles a tile and wave pair.
+  // The running maximum m is the offset of the exponents.  The sums are
+  // rescaled only where some query of the wave has a new one: 64 multiplies,
+  // a quarter of a tile's vector cycles, and none for most tiles once the
+  // maxima have settled.  (Letting scores exceed m by up to 2^8 before it
+  // moves took 3 us off the 4 x 4 x 192 window, but the largest weights then
+  // lie anywhere in their binade and not just below a power of two: the
+  // bf16 weights' error grew, 2.2e-3 to 2.3e-3 of the output.)
+  auto max16 = [](const f32x16_t& s) {  // three levels deep: a dependent instruction costs 8 cycles
+    auto max3 = [](float x, float y, float z) { return fmaxf(fmaxf(x, y), z); };
+    const float u0 = max3(s[0], s[1], s[2]), u1 = max3(s[3], s[4], s[5]), u2 = max3(s[6], s[7], s[8]),
+                u3 = max3(s[9], s[10], s[11]), u4 = max3(s[12], s[13], s[14]);
+    return fmaxf(max3(u0, u1, u2), max3(u3, u4, s[15]));
+  };
+  auto stage_step = [&](auto b_c, auto last_c, int i, f32x16_t& s, f32x16_t& sn) {
+    constexpr int b = decltype(b_c)::value;
+    constexpr bool last = decltype(last_c)::value;
+    wait_vmcnt<0>();
+    lds_barrier();
+    const int nxt2 = scalar(ahead);
+    const uint32_t v_off = tile_off(i + kStageTiles, nxt), k_off = tile_off(i + 2 * kStageTiles, nxt2);
+    const bool on = i + kh < n_vis;  // the last stage may hold one tile
+    if (!(on && (cur & full_bit))) {
+      // the position test per score only where some key of the tile lies
+      // beyond some query of the wave (or past Nk)
+      const int* pos = reinterpret_cast<const int*>(lds + kLdsPos + (kAttnWaves * b + wave) * kPosBytes);
+      const int left = on ? a.Nk - tile_of(cur) * kKeys : 0;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int4 p4 = *reinterpret_cast<const int4*>(pos + 8 * q + 4 * hi);
+        const int pp[4] = {p4.x, p4.y, p4.z, p4.w};
 #pragma unroll
         for (int r = 0; r < 4; ++r)
-          if (l_pos[b][16 * u + 4 * g + r] > pq) s[u][r] = -INFINITY;
+          if (pp[r] > pq || 8 * q + 4 * hi + r >= left) s[4 * q + r] = -INFINITY;
+      }
+      tmax = max16(s);
     }
-    // ---- online softmax over this lane's query (its 8 keys here, then the
-    // 4 lane groups holding the same query), in scaled base-2 units: the
-    // scale is positive, so the largest raw score gives the largest scaled one
-    float tmax = -INFINITY;
+    bf16x8_t kf[8];
+    if constexpr (!last) {
 #pragma unroll
-    for (int u = 0; u < 2; ++u)
+      for (int q = 0; q < 8; ++q) kf[q] = key_frag(b ^ 1, q);
+      issue_pos(b ^ 1, v_off);
+    }
+    // ---- online softmax over this lane's query (its 16 keys here, the
+    // other 16 in lane ^ 32), in scaled base-2 units: the scale is
+    // positive, so the largest raw score gives the largest scaled one
+    const float top = max_xor32(tmax) * sl2;
+    if (__any(top > m)) {
+      const float mnew = fmaxf(m, top);
+      // (while nothing is visible yet m stays -inf and all sums are 0)
+      const float alpha = mnew == -INFINITY ? 1.0f : __builtin_amdgcn_exp2f(m - mnew);
 #pragma unroll
-      for (int r = 0; r < 4; ++r) tmax = fmaxf(tmax, s[u][r]);
-    tmax = max_xor32(max_xor16(tmax)) * sl2;
-    const float mnew = fmaxf(m, tmax);
+      for (int r = 0; r < 4; ++r) ls[r] *= alpha;
+#pragma unroll
+      for (int t4 = 0; t4 < kD / 32; ++t4)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[t4][r] *= alpha;
+      m = mnew;
+    }
     // exponent offset: while nothing is visible yet the masked scores
     // (-inf) must still give 0
-    const float mb = mnew == -INFINITY ? 0.0f : mnew;
-    const float alpha = __builtin_amdgcn_exp2f(m - mb);  // 0 while m is -inf (the sums are 0 then)
-    float p[2][4], psum = 0.0f;
+    const float mb = m == -INFINITY ? 0.0f : m;
+    if constexpr (!last) ahead = tile_at(i + 3 * kStageTiles);
+    // The weights go through three steps a slot or more apart, so that none
+    // waits for the one before: exponent (fma), exponential, then the sum
+    // and the rounding to bf16.
+    uint32_t pw[8];  // weights, two to a word
+    auto expo = [&](int r) { s[r] = __builtin_fmaf(s[r], sl2, -mb); };
+    auto weigh = [&](int r) { s[r] = __builtin_amdgcn_exp2f(s[r]); };
+    auto close = [&](int w) {
+      ls[(2 * w) & 3] += s[2 * w];
+      ls[(2 * w + 1) & 3] += s[2 * w + 1];
+      pw[w] = bf16x2_bits(s[2 * w], s[2 * w + 1]);
+    };
+    union { v4s_t h[2]; bf16x8_t v; } vf[kD / 32][2];
+    auto next_score = [&](int q) {
+      if constexpr (!last) sn = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[q], qf[q], q == 0 ? f32x16_t{} : sn, 0, 0, 0);
+    };
+    auto value_frag = [&](int t4, int j) {  // d block t4, keys 16 j + 8 u + 4 hi ..
 #pragma unroll
-    for (int u = 0; u < 2; ++u)
+      for (int u = 0; u < 2; ++u)
+        vf[t4][j].h[u] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+            (__attribute__((address_space(3))) v4s_t*)(v_rd[t4] + (b * kStageKV + (16 * j + 8 * u) * 256)));
+    };
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        p[u][r] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[u][r], sl2, -mb));
-        psum += p[u][r];
-      }
-    lsum = lsum * alpha + psum;
-    m = mnew;
-    // weights as the B operand: element e of lane group g is key 4 g + e
-    // (e < 4) or 16 + 4 g + (e - 4)
-    const uint4 pw = make_uint4(bf16x2_bits(p[0][0], p[0][1]), bf16x2_bits(p[0][2], p[0][3]),
-                                bf16x2_bits(p[1][0], p[1][1]), bf16x2_bits(p[1][2], p[1][3]));
-    const bf16x8_t pb = as_bf16x8(pw);
-    // ---- O^T += V^T P^T: A row d = 16 t + r16, the same 8 keys
+    for (int r = 0; r < 6; ++r) expo(r);
+    weigh(0);
+    weigh(1);
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int t = 0; t < kD / 16; ++t) {
-      const uint16_t* vr = &l_vt[b][(16 * t + r16) * kVtPitch];
-      const uint2 va = *reinterpret_cast<const uint2*>(vr + 4 * g);
-      const uint2 vb = *reinterpret_cast<const uint2*>(vr + 16 + 4 * g);
-      const bf16x8_t vf = as_bf16x8(make_uint4(va.x, va.y, vb.x, vb.y));
-#pragma unroll
-      for (int r = 0; r < 4; ++r) acc[t][r] *= alpha;
-      acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf, pb, acc[t], 0, 0, 0);
+    for (int q = 0; q < 4; ++q) {  // weights 0 - 7
+      next_score(q);
+      if constexpr (!last)
+        issue_values(b ^ 1, q, v_off);
+      value_frag(q, 0);
+      weigh(2 * q + 2);
+      weigh(2 * q + 3);
+      expo(2 * q + 6);
+      expo(2 * q + 7);
+      close(q);
+      __builtin_amdgcn_sched_barrier(0);
     }
-  };
-
-  // One barrier per tile: stage b is computed while stage b ^ 1 is filled;
-  // stage b ^ 1 was last read before the previous barrier.
-  if (cur < ntiles) {
-    load_tile(cur);
-    store_tile(0);
-  }
-  __syncthreads();
-  int b = 0;
-  while (cur < ntiles) {
-    const int nxt = next_visible(cur + 1);
-    if (nxt < ntiles) load_tile(nxt);
-    compute_tile(b, cur);
-    if (nxt < ntiles) store_tile(b ^ 1);
-    __syncthreads();
-    b ^= 1;
+    // ---- O^T += V^T P^T: the weights are the B operand of MFMA j: elements
+    // 0-3 are keys 16 j + 4 hi .., 4-7 keys 16 j + 8 + 4 hi ..
+    const bf16x8_t pb0 = as_bf16x8(make_uint4(pw[0], pw[1], pw[2], pw[3]));
+    expo(14);
+    expo(15);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {  // weights 8 - 15
+      next_score(4 + q);
+      if constexpr (!last)
+        issue_keys(b, q, k_off);
+      if (q < 3) weigh(10 + 2 * q);
+      if (q > 0) close(3 + q);
+      __builtin_amdgcn_sched_barrier(0);
+      acc[q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[q][0].v, pb0, acc[q], 0, 0, 0);
+      value_frag(q, 1);
+      if (q < 3) weigh(11 + 2 * q);
+      if (q == 3) close(7);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    const bf16x8_t pb1 = as_bf16x8(make_uint4(pw[4], pw[5], pw[6], pw[7]));
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      acc[q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[q][1].v, pb1, acc[q], 0, 0, 0);
+      if constexpr (!last)
+        if (q == 2) {
+          tmax = max16(sn);
+          asm volatile("" : "+v"(tmax));  // here, under the matrix instructions
+        }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) asm volatile("" : "+v"(ls[r]));
     cur = nxt;
+    nxt = nxt2;
+  };
+  if (n_vis > 0) {
+    constexpr std::integral_constant<int, 0> b0{};
+    constexpr std::integral_constant<int, 1> b1{};
+    f32x16_t s0, s1;
+    wait_vmcnt<0>();
+    lds_barrier();
+#pragma unroll
+    for (int n = 0; n < kLoads; ++n) {
+      issue_values(0, n, tile_off(0, cur));
+      issue_keys(1, n, tile_off(kStageTiles, nxt));
+    }
+    issue_pos(0, tile_off(0, cur));
+#pragma unroll
+    for (int q = 0; q < 8; ++q)
+      s0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(key_frag(0, q), qf[q], q == 0 ? f32x16_t{} : s0, 0, 0, 0);
+    tmax = max16(s0);
+    int i = 0;
+    for (; i + 2 * kStageTiles < n_vis; i += 2 * kStageTiles) {
+      stage_step(b0, std::false_type{}, i, s0, s1);
+      stage_step(b1, std::false_type{}, i + kStageTiles, s1, s0);
+    }
+    if (i + kStageTiles < n_vis) {
+      stage_step(b0, std::false_type{}, i, s0, s1);
+      stage_step(b1, std::true_type{}, i + kStageTiles, s1, s0);
+    } else {
+      stage_step(b0, std::true_type{}, i, s0, s1);
+    }
   }
 
-  // ---- O = O^T / l: lane holds query r16, d = 16 t + 4 g + r
-  lsum += __shfl_xor(lsum, 16, 64);
+  // ---- the two key halves of each query group meet: wave kh finishes d
+  // blocks 2 kh, 2 kh + 1 and hands the others, with its maximum and weight
+  // total, to its partner through the idle stages
+  float lsum = (ls[0] + ls[1]) + (ls[2] + ls[3]);
   lsum += __shfl_xor(lsum, 32, 64);
+  wait_vmcnt<0>();
+  lds_barrier();  // every wave is done with the stages
+  float* xo = reinterpret_cast<float*>(lds) + wave * (32 * 64);  // 8 KiB per wave
+  float* xml = reinterpret_cast<float*>(lds + kAttnWaves * 8192);
+#pragma unroll
+  for (int u = 0; u < 2; ++u)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) xo[(16 * u + r) * 64 + lane] = kh == 0 ? acc[2 + u][r] : acc[u][r];
+  if (hi == 0) *reinterpret_cast<float2*>(xml + (wave * 32 + l32) * 2) = make_float2(m, lsum);
+  lds_barrier();
+  const int other = wave ^ 2;
+  const float2 ml2 = *reinterpret_cast<const float2*>(xml + (other * 32 + l32) * 2);
+  const float mt = fmaxf(m, ml2.x), mtb = mt == -INFINITY ? 0.0f : mt;
+  const float w0 = __builtin_amdgcn_exp2f(m - mtb), w1 = __builtin_amdgcn_exp2f(ml2.x - mtb);
+  const float l = lsum * w0 + ml2.y * w1;
+  const float* xr = reinterpret_cast<const float*>(lds) + other * (32 * 64);
+  float o[2][16];
+#pragma unroll
+  for (int u = 0; u < 2; ++u)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) o[u][r] = (kh == 0 ? acc[u][r] : acc[2 + u][r]) * w0 + xr[(16 * u + r) * 64 + lane] * w1;
+
+  // ---- O = O^T / l: lane holds query l32, d = 32 (2 kh + u) + 8 q + 4 hi + r
   if (!q_ok) return;
   if (!final_out) {
     // a split's partial result: the unnormalized sum, its running maximum
     // (base 2, scaled scores) and weight total; attn_combine merges them
     const size_t row = ((size_t)split * a.H + h) * a.Nq + qi;
-    float* po = a.part_o + row * kD;
-    if (m != -INFINITY)  // the merge reads no sum of a split that saw nothing
+    float* po = a.part_o + row * kD + 64 * kh + 4 * hi;
+    if (mt != -INFINITY)  // the merge reads no sum of a split that saw nothing
 #pragma unroll
-      for (int t = 0; t < kD / 16; ++t)
-        *reinterpret_cast<float4*>(po + 16 * t + 4 * g) = make_float4(acc[t][0], acc[t][1], acc[t][2], acc[t][3]);
-    if (g == 0) *reinterpret_cast<float2*>(a.part_ml + row * 2) = make_float2(m, lsum);
+      for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          *reinterpret_cast<float4*>(po + 32 * u + 8 * q) = make_float4(o[u][4 * q], o[u][4 * q + 1], o[u][4 * q + 2], o[u][4 * q + 3]);
+    if (hi == 0 && kh == 0) *reinterpret_cast<float2*>(a.part_ml + row * 2) = make_float2(mt, l);
     return;
   }
-  const float inv = lsum > 0.0f ? __fdiv_rn(1.0f, lsum) : 0.0f;  // a query that sees no key gets 0
-  uint16_t* orow = a.o + ((size_t)h * a.Nq + qi) * kD;
+  const float inv = l > 0.0f ? __fdiv_rn(1.0f, l) : 0.0f;  // a query that sees no key gets 0
+  uint16_t* orow = a.o + ((size_t)h * a.Nq + qi) * kD + 64 * kh + 4 * hi;
 #pragma unroll
-  for (int t = 0; t < kD / 16; ++t) {
-    const uint2 w = make_uint2(bf16x2_bits(acc[t][0] * inv, acc[t][1] * inv), bf16x2_bits(acc[t][2] * inv, acc[t][3] * inv));
-    *reinterpret_cast<uint2*>(orow + 16 * t + 4 * g) = w;
-  }
+  for (int u = 0; u < 2; ++u)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const uint2 w = make_uint2(bf16x2_bits(o[u][4 * q] * inv, o[u][4 * q + 1] * inv),
+                                 bf16x2_bits(o[u][4 * q + 2] * inv, o[u][4 * q + 3] * inv));
+      *reinterpret_cast<uint2*>(orow + 32 * u + 8 * q) = w;
+    }
 }
-
 
 // Merge of the splits' partial results: thread per (head, query, 8 of d).
 __global__ __launch_bounds__(256) void attn_combine(const AttnArgs a) {
@@ -620,7 +830,7 @@ hipError_t launch_stream_attention(const AttnArgs& a0, hipStream_t stream) {
   const unsigned X = (unsigned)((a.Nq + kQPerBlock - 1) / kQPerBlock);
   // scheduled calls (at most kSchedMaxClasses x 4096 items) take a 1-D grid
   const dim3 grid = a.sched ? dim3(X * (unsigned)a.H * (unsigned)a.S) : dim3(X, (unsigned)a.H, (unsigned)a.S);
-  stream_attention<<<grid, dim3(kAttnWaves * 64), 0, stream>>>(a);
+  stream_attention<<<grid, dim3(kAttnWaves * 64), kLdsAttn, stream>>>(a);
   if (a.S > 1) {
     const size_t threads = (size_t)a.H * a.Nq * (kD / 8);
     attn_combine<<<dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, stream>>>(a);

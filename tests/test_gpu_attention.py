@@ -225,3 +225,36 @@ def test_rejected_calls():
     # a split shape without its workspace
     assert w.w4a8_stream_attention_workspace_bytes(32, 768, 3072) > 0
     assert f(*args(H=32, Hkv=8, Nq=768, Nk=3072)) == w.W4A8_EINVAL
+
+
+@pytest.mark.parametrize("V,F,T,H,Hkv", [(1, 1, 33, 8, 8), (1, 3, 32, 16, 4), (2, 2, 48, 24, 8), (1, 2, 65, 28, 4)])
+def test_stage_and_head_remainders(V, F, T, H, Hkv):
+    # an odd number of visible tiles (the last two-tile stage holds one), a
+    # lone tile, a partial second query half, and head counts that the
+    # workgroups' order does (8, 16, 24) and does not (28) regroup
+    pos_k, pos_q = window(V, F, T, F - 1)
+    check(H, Hkv, pos_q, pos_k, 820 + T, f"remainders {V}x{F}x{T}")
+
+
+@pytest.mark.parametrize("steps", ["rising", "falling", "slow", "zigzag"])
+def test_running_maximum_moves(steps):
+    # tile t's scores lie near level[t] (base-2 units): the running maximum,
+    # and with it the sums' rescale, moves far at every tile, at the first
+    # only, a little at every tile, or at some.
+    Nk, Nq, ntiles = 320, 64, 10
+    t = np.arange(ntiles)
+    level = {"rising": 15.0 * t, "falling": 15.0 * (ntiles - t), "slow": 3.0 * t, "zigzag": 20.0 * (t % 2)}[steps]
+    rng = np.random.Generator(np.random.PCG64(830))
+    q = I.to_bf16_bits(np.ones((1, Nq, D), np.float32))
+    # score = sum_d k_d * scale; scale log2(e) * D * mean(k) = level
+    scale = np.float32(1.0)
+    mean = level / (D * 1.4426950408889634)
+    k = np.repeat(mean, 32)[:, None] + 0.01 * rng.standard_normal((Nk, D))
+    k = I.to_bf16_bits(k[None].astype(np.float32))
+    v = I.activations(Nk, D, 831).reshape(1, Nk, D)
+    pos_q, pos_k = np.full(Nq, Nk, np.int32), np.arange(Nk, dtype=np.int32)
+    cos_t, sin_t = np.ones((Nk + 1, D // 2), np.float32), np.zeros((Nk + 1, D // 2), np.float32)
+    print(f"[case] running maximum {steps}", flush=True)
+    o = run(q, k, v, pos_q, pos_k, cos_t, sin_t, float(scale))
+    o64, bnd = oracle.streaming_attention(q, k, v, pos_q, pos_k, cos_t, sin_t, scale)
+    assert (np.abs(o - o64) <= 2.0 ** -8 * np.abs(o64) + 2.0 ** -8 * bnd + 1e-30).all()
