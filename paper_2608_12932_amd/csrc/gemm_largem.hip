@@ -67,8 +67,9 @@ LargeMPlan plan_largem(int M, int N, int K, bool group, bool swiglu) {
     p.threads = 64 * kMenu[p.cfg].GM * kMenu[p.cfg].GN * kMenu[p.cfg].ks;
   }
   const TileCfg& c = kMenu[p.cfg];
-  p.lds_bytes = (size_t)c.ring * ((size_t)p.BM * 128 + (size_t)p.BN / 16 * kBlockBytes +
-                                  (group ? (size_t)(c.GM * c.GN) * 256 : 0));
+  const int ring = group && p.cfg == 1 ? kGroup128Ring : c.ring;
+  p.lds_bytes = (size_t)ring * ((size_t)p.BM * 128 + (size_t)p.BN / 16 * kBlockBytes +
+                                (group ? (size_t)(c.GM * c.GN) * 256 : 0));
   return p;
 }
 

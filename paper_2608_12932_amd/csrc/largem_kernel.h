@@ -82,6 +82,7 @@ constexpr TileCfg kMenu[] = {
 };
 constexpr int kMenuKSplit = 4;  // the k-split form of entry 2
 constexpr int kMenuSize = sizeof(kMenu) / sizeof(kMenu[0]);
+constexpr int kGroup128Ring = 3;  // entry 1 with group scales has its own kernel (gemm_largem_group.hip)
 
 template <int WM, int WN, int GM, int GN, bool GROUP, int kRing, bool SW, int KS = 1>
 __global__ __launch_bounds__(GM * GN * 64 * KS) void largem(const LargeMArgs a) {
