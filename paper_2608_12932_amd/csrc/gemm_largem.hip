@@ -58,6 +58,29 @@ LargeMPlan plan_largem(int M, int N, int K, bool group, bool swiglu) {
       p.tiles = tiles;
     }
   }
+  // Plain group scales choose between the 128 x 128 and the 64 x 64 tile by
+  // the time of the fullest CU, in us for 32 steps (K = 4096) beyond what
+  // every call pays: a lone 128 x 128 tile 19.8 and one of several 16 (two
+  // share the CU), a lone 64 x 64 tile 6.4 (its k-split form) and one of
+  // several 5.5.  Fitted to a sweep of both over M = 80 .. 2048 and
+  // N = 1536 .. 24576; at the turns, 128 x 128 against 64 x 64 in us:
+  // qkv M = 768 34.3 / 30.4 (2 tiles a CU against 5), M = 1024 34.1 / 39.5
+  // (2, 6); gate+up M = 320 50.8 / 47.7 (3, 8), M = 384 51.0 / 54.2 (3, 9);
+  // o M = 768 23.6 / 20.6 (1, 3), M = 1024 24.1 / 28.1 (1, 4).
+  if (group && !swiglu) {
+    auto tiles_of = [&](int B) { return (int64_t)((M + B - 1) / B) * ((N + B - 1) / B); };
+    auto cost = [](int64_t tiles, double lone, double each) {
+      const double n = (double)((tiles + 255) / 256);
+      return n <= 1 ? lone : n * each;
+    };
+    p.cfg = cost(tiles_of(128), 19.8, 16.0) < cost(tiles_of(64), 6.4, 5.5) ? 1 : 2;
+    const int B = p.cfg == 1 ? 128 : 64;
+    p.BM = p.BN = B;
+    p.threads = 256;
+    p.tiles_m = (M + B - 1) / B;
+    p.tiles_n = (N + B - 1) / B;
+    p.tiles = tiles_of(B);
+  }
   // 64 x 64 tiles that fill at most one round: two k groups per tile
   // (measured at M = 256, group scales: o 12.4 -> 10.8 us, down 31.8 -> 24.4
   // us; channel scales: down 24.0 -> 21.7 us, o unchanged; with more tiles,

@@ -1,0 +1,27 @@
+"""The 128 x 128 group-scale tile at its edges (1 to 7 steps on its 3-deep
+stage ring, ragged row and column tails) against the oracle, and the sizes at
+which the planner turns from one group tile to the other."""
+import numpy as np
+import pytest
+
+import paper_2608_12932_amd as w
+from paper_2608_12932_amd import inputs as I
+from helpers import check_all_outputs
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,N", [(2000, 6160), (1793, 6128)])
+@pytest.mark.parametrize("steps", [1, 2, 3, 4, 5, 6, 7])
+def test_group_tile_edges(steps, M, N):
+    K = 128 * steps
+    assert "largem<128x128,group>" in w.w4a8_linear_describe(M, N, K, w.SCALE_GROUP_F16)
+    x = I.activations(M, K, 840 + M + steps)
+    W, s = I.weights(N, K, 850 + N + steps, group=True)
+    rows = np.unique(np.concatenate([np.arange(0, M, 61), np.arange(M - 40, M)]))  # with the ragged last row tile
+    check_all_outputs(x, W, s, group=True, rows=rows, label="group tile")
+
+
+@pytest.mark.parametrize("M,N,tile", [(768, 6144, 64), (1024, 6144, 128), (320, 24576, 64), (384, 24576, 128),
+                                      (768, 4096, 64), (1024, 4096, 128), (256, 24576, 128), (192, 24576, 64)])
+def test_group_tile_choice(M, N, tile):
+    assert f"largem<{tile}x{tile},group" in w.w4a8_linear_describe(M, N, 4096, w.SCALE_GROUP_F16)
