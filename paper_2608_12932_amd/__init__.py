@@ -1,7 +1,7 @@
 """MI355X (gfx950) W4A8 linear layer: Python binding of libw4a8.so.
 
 The functions carry the names of the C ABI in include/w4a8.h and only
-marshal arguments: they check dtypes and shapes of torch tensors, allocate
+marshal arguments (the plain case of the hot ones in csrc/binding.cpp): they check dtypes and shapes of torch tensors, allocate
 outputs with torch (device memory is the one thing torch is used for here),
 and pass raw pointers plus torch's current HIP stream to the library.  Every
 step of the computation runs in the HIP kernels; there is no fallback, and
@@ -42,6 +42,18 @@ class W4A8Error(RuntimeError):
 
 
 _lib = None
+_fast = None
+
+
+def _load_fast():
+    """The native fast path of the hot calls (csrc/binding.cpp)."""
+    global _fast
+    if _fast is None:
+        lib()
+        from . import _native
+
+        _fast = _native
+    return _fast
 
 
 def lib() -> ctypes.CDLL:
@@ -147,6 +159,10 @@ def w4a8_pack_weights(w: torch.Tensor, out: torch.Tensor | None = None, stream=N
 
 def w4a8_quantize_act(x: torch.Tensor, stream=None):
     """x: bf16 [M][K] device tensor -> (codes int8 [M][K], scales fp32 [M])."""
+    if stream is None:
+        r = (_fast or _load_fast()).quantize(x)
+        if r is not None:
+            return r if type(r) is tuple else _check(r, "w4a8_quantize_act")
     M, K = x.shape
     with _alloc_on(stream):
         q = torch.empty((M, K), dtype=torch.int8, device=x.device)
@@ -161,6 +177,10 @@ def w4a8_rmsnorm_quantize_act(x: torch.Tensor, gamma: torch.Tensor, eps: float, 
     """RMSNorm (gain gamma bf16 [K], eps > 0) of bf16 x [M][K] then the
     per-token int8 quantize of the fp32 result -> (codes int8 [M][K],
     scales fp32 [M]), the int8 input of w4a8_linear."""
+    if stream is None:
+        r = (_fast or _load_fast()).quantize(x, gamma, eps)
+        if r is not None:
+            return r if type(r) is tuple else _check(r, "w4a8_rmsnorm_quantize_act")
     M, K = x.shape
     x_ptr = _dev(x, "x", torch.bfloat16)
     g_ptr = _dev(gamma, "gamma", torch.bfloat16)
@@ -192,6 +212,10 @@ def w4a8_flow_step(x: torch.Tensor, v_new, v_cache: torch.Tensor, dt: float, sta
     v_new) or None (a reused step: v = v_cache).  With stats (evaluated
     steps only) returns fp64 [B][4] = (v.c, v.v, c.c, |v - c|^2) against
     the cache before the step, else None."""
+    if stream is None:
+        r = (_fast or _load_fast()).flow_step(x, v_new, v_cache, dt, stats, repeat)
+        if r is not None:
+            return r if stats and type(r) is not int else None if r is True else _check(r, "w4a8_flow_step")
     B, n = x.shape
     x_ptr = _dev(x, "x", torch.float32)
     c_ptr = _dev(v_cache, "v_cache", torch.bfloat16)
@@ -230,13 +254,15 @@ class Workspace:
     def __init__(self, device="cuda"):
         self.device = torch.device(device)
         self.buf = torch.zeros(0, dtype=torch.uint8, device=self.device)
+        self._home = (self.buf, None)  # the buffer and the stream that its memory is ordered on (None: empty)
 
     def get(self, nbytes: int, stream: torch.cuda.Stream | None = None) -> torch.Tensor:
         s = _torch_stream(stream, self.device)
         if nbytes > self.buf.numel():
             old = self.buf
-            with torch.cuda.stream(s):
+            with contextlib.nullcontext() if stream is None else torch.cuda.stream(s):
                 self.buf = torch.zeros(max(nbytes, 2 * old.numel()), dtype=torch.uint8, device=self.device)
+            self._home = (self.buf, s.cuda_stream)
             if old.numel():
                 old.record_stream(s)
         elif self.buf.numel():
@@ -260,6 +286,26 @@ def _workspace_ptr(workspace, need: int, device, stream):
     else:
         buf = workspace
     return _dev(buf, "workspace", torch.uint8), buf.numel()
+
+
+def _linear_fast(swiglu: int, x, w_packed, w_scale, N, x_scale, scale_mode, out_kind, out, workspace):
+    """The native path of both linear calls on the current stream; None where
+    it does not take the call (a Workspace that has to grow or that belongs
+    to another stream, arguments that need an error, ...)."""
+    buf, home, own = workspace, None, False
+    if type(workspace) is Workspace:
+        own = True
+        buf, home = workspace._home
+        if buf is not workspace.buf:
+            buf = home = None
+    fast = _fast or _load_fast()
+    r = fast.linear(swiglu, x, w_packed, w_scale, N, x_scale, scale_mode, out_kind, out, buf, home, own)
+    if type(r) is int:
+        if r < 0:  # the bytes that the Workspace, on this stream or still empty, lacks
+            workspace.get(-r)
+            return _linear_fast(swiglu, x, w_packed, w_scale, N, x_scale, scale_mode, out_kind, out, workspace)
+        _check(r, "w4a8_linear_swiglu" if swiglu else "w4a8_linear")
+    return r
 
 
 def _linear_call(entry: str, x, w_packed, w_scale, N, out_cols, x_scale, scale_mode, out_kind, out,
@@ -305,6 +351,10 @@ def w4a8_linear(x: torch.Tensor, w_packed: torch.Tensor, w_scale: torch.Tensor |
     x_scale fp32 [M].  w_scale is fp32 [N] (SCALE_CHANNEL_F32) or fp16
     [K/128][N] (SCALE_GROUP_F16).  Returns bf16, fp32 or int32 [M][N].
     """
+    if stream is None:
+        y = _linear_fast(0, x, w_packed, w_scale, N, x_scale, scale_mode, out_kind, out, workspace)
+        if y is not None:
+            return y
     return _linear_call("w4a8_linear", x, w_packed, w_scale, N, N, x_scale, scale_mode, out_kind, out,
                         workspace, stream)
 
@@ -355,6 +405,10 @@ def w4a8_linear_swiglu(x: torch.Tensor, w_packed: torch.Tensor, w_scale: torch.T
     w4a8_linear over weight rows [0, N/2) (gate) and [N/2, N) (up) of the
     same packed weight.  Arguments as for w4a8_linear; out_kind bf16 or fp32.
     """
+    if stream is None:
+        y = _linear_fast(1, x, w_packed, w_scale, N, x_scale, scale_mode, out_kind, out, workspace)
+        if y is not None:
+            return y
     return _linear_call("w4a8_linear_swiglu", x, w_packed, w_scale, N, N // 2, x_scale, scale_mode, out_kind,
                         out, workspace, stream)
 

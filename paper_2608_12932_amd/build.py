@@ -40,9 +40,36 @@ CEILING_SOURCES = ["ceiling.hip"]
 CEILING_LIB = os.path.join(PKG, "libw4a8_ceiling.so")
 
 
+# the binding's native fast path: a CPython extension on torch's C++ API
+NATIVE_SOURCE = "binding.cpp"
+NATIVE_LIB = os.path.join(PKG, "_native.so")
+
+
+def _build_native() -> None:
+    import sysconfig
+
+    import torch
+
+    tdir = os.path.dirname(torch.__file__)
+    inc = [INCLUDE, os.path.join(tdir, "include"), os.path.join(tdir, "include", "torch", "csrc", "api", "include"),
+           sysconfig.get_paths()["include"], os.path.join(os.path.dirname(os.path.dirname(HIPCC)), "include")]
+    tlib = os.path.join(tdir, "lib")
+    tmp = NATIVE_LIB + ".tmp"
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}"]
+    for i in inc:
+        cmd += ["-isystem", i]
+    cmd += [os.path.join(CSRC, NATIVE_SOURCE), "-o", tmp, LIB, "-L", tlib, "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip",
+            "-Wl,-rpath,$ORIGIN", f"-Wl,-rpath,{tlib}"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"building {NATIVE_SOURCE} failed:\n{r.stdout}\n{r.stderr}")
+    os.replace(tmp, NATIVE_LIB)
+
+
 def _link(objs, lib):
     tmp = lib + ".tmp"
-    r = subprocess.run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp, *objs],
+    r = subprocess.run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", f"-Wl,-soname,{os.path.basename(lib)}", "-o", tmp, *objs],
                        capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError(f"link failed:\n{r.stdout}\n{r.stderr}")
@@ -56,6 +83,7 @@ def build() -> str:
         objs = dict(zip(srcs, ex.map(_compile, srcs)))
     _link([objs[s] for s in SOURCES], LIB)
     _link([objs[s] for s in CEILING_SOURCES], CEILING_LIB)
+    _build_native()
     return LIB
 
 
