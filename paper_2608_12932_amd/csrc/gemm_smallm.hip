@@ -47,6 +47,9 @@ constexpr int kOperandVgprsFused = 112;  // the fused path also holds the x chun
 constexpr int kLdsHeader = 256;   // per-row absmax / s / inv / mode
 constexpr int kMaxTilesPerWave = 12;
 constexpr int kMaxFusedTiles = 2;  // fused quantize pays off up to this many tiles
+constexpr int kXtMinRows = 12;     // codes loaded as rows (XT) from this many rows on ...
+// ... and for these tiles (see plan_smallm)
+constexpr bool xt_tiles(int MT, int NT, bool SW) { return MT == 1 ? NT <= 2 : MT > 2 || NT < 6 || SW; }
 constexpr int kFusedMinKB = 256;   // ... and from this many 128-k blocks (K >= 32768) on
 // LDS words per wave tile of partial sums in the reduction: 256 plus a
 // 16-word skew, so that consecutive tiles start 16 banks apart
@@ -111,7 +114,7 @@ struct Emit {
   }
 };
 
-template <int MT, int NT, bool GROUP, int QM, bool EXACT, bool SWIGLU>
+template <int MT, int NT, bool GROUP, int QM, bool EXACT, bool SWIGLU, bool XT>
 __global__ __launch_bounds__(kThreads) void smallm(const SmallMArgs a) {
   static_assert(!SWIGLU || NT % 2 == 0, "gated instances pair gate and up tiles");
   constexpr int HT = SWIGLU ? NT / 2 : NT;  // output column tiles per workgroup
@@ -212,11 +215,21 @@ __global__ __launch_bounds__(kThreads) void smallm(const SmallMArgs a) {
     if constexpr (!FUSED) {
 #pragma unroll
       for (int mt = 0; mt < MT; ++mt) {
-        const int row = mt * 16 + r16;
-        const uint32_t off = ok && row < M ? (uint32_t)(row * K + g4 * 32) : kOOB;
         const uint32_t so = (uint32_t)((ok ? kb : 0) * 128);
-        ab[slot][mt][0] = buf_load16s(xres, off, so);
-        ab[slot][mt][1] = buf_load16s(xres, off == kOOB ? kOOB : off + 16, so);
+        if constexpr (XT) {
+          // 8 whole 128-byte rows per instruction, lane l being chunk l % 8
+          // of row l / 8 (+ 8): turned into operands by compute_stage
+          const int row = mt * 16 + (lane >> 3);
+          const uint32_t off = (uint32_t)(row * K + (lane & 7) * 16);
+          ab[slot][mt][0] = buf_load16s(xres, ok && row < M ? off : kOOB, so);
+          ab[slot][mt][1] = buf_load16s(xres, ok && row + 8 < M ? off + 8 * K : kOOB, so);
+        } else {
+          // the operand itself, two chunks of 16 rows
+          const int row = mt * 16 + r16;
+          const uint32_t off = ok && row < M ? (uint32_t)(row * K + g4 * 32) : kOOB;
+          ab[slot][mt][0] = buf_load16s(xres, off, so);
+          ab[slot][mt][1] = buf_load16s(xres, off == kOOB ? kOOB : off + 16, so);
+        }
       }
     }
   };
@@ -318,6 +331,27 @@ __global__ __launch_bounds__(kThreads) void smallm(const SmallMArgs a) {
     lds_barrier();
   }
 
+  // ---- XT: the wave's own LDS area through which a block's codes turn from
+  // rows (as loaded) into MFMA operands.  Loaded as operands, every
+  // instruction touches all 16 rows' 128-byte lines for half their bytes;
+  // as rows, 8 whole lines: M = 48 on qkv (group) 10.67 -> 9.27 us a call.
+  // Lane (row r16, group g4) takes the
+  // chunks 2 g4 and 2 g4 + 1 of its row.  Chunk c of row r lies at
+  // c ^ ((r >> 1) & 7): 16 rows read at once fall on distinct banks.  LDS
+  // serves a wave in order, so neither a barrier nor a wait is needed.  With
+  // two column tiles or more the area is the wave's part of the reduction's.
+  const uint8_t *xw_lo = nullptr, *xw_hi = nullptr;
+  uint8_t *xw_wr = nullptr, *xw_wr8 = nullptr;
+  if constexpr (XT) {
+    uint8_t* xw = l_body + (NT >= 2 ? wave * (MT * NT * kRedTile * 4)
+                                    : kWaves * MT * NT * kRedTile * 4 + wave * (MT * 2048));
+    const int wr_row = lane >> 3, rsw = (r16 >> 1) & 7;
+    xw_wr = xw + wr_row * 128 + (((lane & 7) ^ (wr_row >> 1)) << 4);               // rows 0 - 7
+    xw_wr8 = xw + (8 + wr_row) * 128 + (((lane & 7) ^ (4 + (wr_row >> 1))) << 4);  // rows 8 - 15
+    xw_lo = xw + r16 * 128 + (((2 * g4) ^ rsw) << 4);
+    xw_hi = xw + r16 * 128 + (((2 * g4 + 1) ^ rsw) << 4);
+  }
+
   // ---- main loop
   v4i acc[MT][NT];
   float facc[GROUP ? MT : 1][NT][4];
@@ -349,11 +383,21 @@ __global__ __launch_bounds__(kThreads) void smallm(const SmallMArgs a) {
       const uint8_t* p = l_body + min(r16, M - 1) * ldq + (kb - kb_begin) * 128 + g4 * 32;
       alo[0] = *reinterpret_cast<const v4i*>(p);
       ahi[0] = *reinterpret_cast<const v4i*>(p + 16);
-    } else {
+    } else if constexpr (!XT) {
 #pragma unroll
       for (int mt = 0; mt < MT; ++mt) {
         alo[mt] = as_v4i(ab[s][mt][0]);
         ahi[mt] = as_v4i(ab[s][mt][1]);
+      }
+    } else {
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+        for (int e = 0; e < 2; ++e) *reinterpret_cast<uint4*>((e ? xw_wr8 : xw_wr) + mt * 2048) = ab[s][mt][e];
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt) {
+        alo[mt] = *reinterpret_cast<const v4i*>(xw_lo + mt * 2048);
+        ahi[mt] = *reinterpret_cast<const v4i*>(xw_hi + mt * 2048);
       }
     }
 #pragma unroll
@@ -539,35 +583,49 @@ typedef void (*SmallMKernel)(const SmallMArgs);
 // and in-flight operands no longer fit in 256 registers.  Group kernels
 // have no EXACT form (the planner never asks for one); gated kernels need
 // an even NT.
+// XT instances: see plan_smallm.
 template <int MT, int NT, bool GROUP, int QM, bool SW>
-SmallMKernel instance(bool exact) {
-  if constexpr (MT * NT > kMaxTilesPerWave || (QM != kQNone && MT != 1) || (SW && NT % 2))
+SmallMKernel instance(bool exact, bool xt) {
+  if constexpr (MT * NT > kMaxTilesPerWave || (QM != kQNone && MT != 1) || (SW && NT % 2)) {
     return nullptr;
-  else if constexpr (GROUP)
-    return exact ? nullptr : smallm<MT, NT, GROUP, QM, false, SW>;
-  else
-    return exact ? smallm<MT, NT, GROUP, QM, true, SW> : smallm<MT, NT, GROUP, QM, false, SW>;
+  } else {
+    // the forms that exist
+    constexpr bool kXt = QM == kQNone && xt_tiles(MT, NT, SW), kPlain = MT == 1 || !kXt;
+    if constexpr (kXt)
+      if (xt) {
+        if constexpr (!GROUP)
+          if (exact) return smallm<MT, NT, GROUP, QM, true, SW, true>;
+        return exact ? nullptr : smallm<MT, NT, GROUP, QM, false, SW, true>;
+      }
+    if (xt) return nullptr;
+    if constexpr (kPlain) {
+      if constexpr (!GROUP)
+        if (exact) return smallm<MT, NT, GROUP, QM, true, SW, false>;
+      return exact ? nullptr : smallm<MT, NT, GROUP, QM, false, SW, false>;
+    }
+    return nullptr;
+  }
 }
 
 template <int MT, bool GROUP, int QM, bool SW>
-SmallMKernel pick_nt(int NT, bool exact) {
+SmallMKernel pick_nt(int NT, bool exact, bool xt) {
   switch (NT) {
-    case 1: return instance<MT, 1, GROUP, QM, SW>(exact);
-    case 2: return instance<MT, 2, GROUP, QM, SW>(exact);
-    case 3: return instance<MT, 3, GROUP, QM, SW>(exact);
-    case 4: return instance<MT, 4, GROUP, QM, SW>(exact);
-    case 6: return instance<MT, 6, GROUP, QM, SW>(exact);
+    case 1: return instance<MT, 1, GROUP, QM, SW>(exact, xt);
+    case 2: return instance<MT, 2, GROUP, QM, SW>(exact, xt);
+    case 3: return instance<MT, 3, GROUP, QM, SW>(exact, xt);
+    case 4: return instance<MT, 4, GROUP, QM, SW>(exact, xt);
+    case 6: return instance<MT, 6, GROUP, QM, SW>(exact, xt);
     default: return nullptr;
   }
 }
 
 template <bool GROUP, bool SW>
 SmallMKernel pick_group(const SmallMPlan& p) {
-  if (p.qmode == kQLds) return pick_nt<1, GROUP, kQLds, SW>(p.NT, p.exact);
+  if (p.qmode == kQLds) return pick_nt<1, GROUP, kQLds, SW>(p.NT, p.exact, p.xt);
   switch (p.MT) {
-    case 1: return pick_nt<1, GROUP, kQNone, SW>(p.NT, p.exact);
-    case 2: return pick_nt<2, GROUP, kQNone, SW>(p.NT, p.exact);
-    case 4: return pick_nt<4, GROUP, kQNone, SW>(p.NT, p.exact);
+    case 1: return pick_nt<1, GROUP, kQNone, SW>(p.NT, p.exact, p.xt);
+    case 2: return pick_nt<2, GROUP, kQNone, SW>(p.NT, p.exact, p.xt);
+    case 4: return pick_nt<4, GROUP, kQNone, SW>(p.NT, p.exact, p.xt);
     default: return nullptr;
   }
 }
@@ -671,9 +729,20 @@ SmallMPlan plan_smallm(int M, int N, int K, bool group, bool bf16_in, bool swigl
     const int it_full = (kbs + kWaves - 1) / kWaves, it_last = (last + kWaves - 1) / kWaves;
     p.exact = !group && it_full % D == 0 && it_last % D == 0;
   }
+  // Codes loaded as rows (XT) or as operands: as rows where the codes weigh
+  // against the weights, i.e. with several row tiles, or with one of 12
+  // rows or more and few column tiles.  us a call on int8 codes, operands /
+  // rows: down M = 4 9.30 / 10.20, M = 9 10.4 / 10.8 (both with the quantize),
+  // M = 12 7.69 / 7.69, M = 16 8.72 / 8.30,
+  // M = 32 14.1 / 11.1, M = 64 26.3 / 17.9 (group scales 26.8 / 16.1); qkv
+  // M = 64 11.2 / 8.7; gate+up M = 16 (6 tiles) 9.86 / 10.0, M = 64 24.6 /
+  // 17.8, gated M = 32 12.1 / 11.7; but plain gate+up at M = 24 (2 row by 6
+  // column tiles, out of registers) 11.3 / 11.6, group scales 12.5 / 15.0.
+  p.xt = p.qmode == kQNone && M >= kXtMinRows && xt_tiles(p.MT, p.NT, swiglu);
   const size_t red = (size_t)kWaves * p.MT * p.NT * kRedTile * 4;
   const size_t codes = p.qmode == kQLds ? ((size_t)M * (kbs * 128 + 16) + 15) / 16 * 16 : 0;
-  p.lds_bytes = kLdsHeader + codes + red;
+  // (one column tile: the waves' operand areas lie past the reduction's)
+  p.lds_bytes = kLdsHeader + codes + red + (p.xt && p.NT == 1 ? (size_t)kWaves * p.MT * 2048 : 0);
   return p;
 }
 

@@ -53,6 +53,7 @@ struct SmallMPlan {
   int tpr;               // fused quantize: threads per token row
   bool exact;            // every wave's block count is a multiple of the stage depth
   bool swiglu;           // gated output silu(gate) * up (gate columns [0, N/2), up [N/2, N))
+  bool xt;               // codes loaded as rows and turned into operands through LDS
   size_t lds_bytes;
   double model_us;       // the cost model's time for the GEMM launch (int8 codes in)
 };

@@ -1,4 +1,5 @@
-"""The 128 x 128 group-scale tile at its edges (1 to 7 steps on its 3-deep
+"""Kernel forms at their edges: the rows form of the small-M codes; the 128 x
+128 group-scale tile (1 to 7 steps on its 3-deep
 stage ring, ragged row and column tails) against the oracle, and the sizes at
 which the planner turns from one group tile to the other."""
 import numpy as np
@@ -25,3 +26,16 @@ def test_group_tile_edges(steps, M, N):
                                       (768, 4096, 64), (1024, 4096, 128), (256, 24576, 128), (192, 24576, 64)])
 def test_group_tile_choice(M, N, tile):
     assert f"largem<{tile}x{tile},group" in w.w4a8_linear_describe(M, N, 4096, w.SCALE_GROUP_F16)
+
+
+# The small-M kernels load the codes as whole rows from 12 rows on: the turn,
+# the edges of the 8-row halves and 16-row tiles, one and several column
+# tiles, K splits that leave waves without a block.
+@pytest.mark.gpu
+@pytest.mark.parametrize("group", [False, True])
+@pytest.mark.parametrize("M", [11, 12, 15, 16, 17, 25, 33, 40, 48, 57, 64])
+def test_rows_of_codes(M, group):
+    for K, N in ((128, 48), (1152, 4096), (2048, 8192)):
+        x = I.activations(M, K, 860 + M)
+        W, s = I.weights(N, K, 861 + N, group=group)
+        check_all_outputs(x, W, s, group=group, label="rows of codes")
