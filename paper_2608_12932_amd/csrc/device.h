@@ -22,6 +22,8 @@
 #include <stdint.h>
 #include <string.h>
 
+#include <type_traits>
+
 namespace w4a8 {
 
 typedef int v4i __attribute__((ext_vector_type(4)));
@@ -125,13 +127,47 @@ __device__ __forceinline__ uint32_t fold_pair_max(uint32_t acc) {
   return lo > hi ? lo : hi;
 }
 
-__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
+// Wave reductions by lane moves in the vector unit (quad permutes, mirrors
+// within 8 and 16 lanes, row swaps): ~8 cycles a step, where a shuffle goes
+// through the LDS pipeline.  Every lane gets the result.  (A mirror serves
+// as the exchange with lane ^ 4 or ^ 8, the steps before having made the
+// lanes of each group equal.)
+template <int kCtrl>
+__device__ __forceinline__ uint32_t lane_move(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, kCtrl, 0xF, 0xF, false);
+}
+constexpr int kXor1 = 0xB1, kXor2 = 0x4E, kMirror8 = 0x141, kMirror16 = 0x140;
+template <class T, class F>
+__device__ __forceinline__ T wave_reduce(T v, F op) {
+  constexpr int W = sizeof(T) / 4;
+  struct Words { uint32_t w[W]; };
+  auto step = [&](auto ctrl) {
+    Words a = __builtin_bit_cast(Words, v);
 #pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) {
-    uint32_t o = (uint32_t)__shfl_xor((int)v, off, 64);
-    v = v > o ? v : o;
+    for (int i = 0; i < W; ++i) a.w[i] = lane_move<decltype(ctrl)::value>(a.w[i]);
+    v = op(v, __builtin_bit_cast(T, a));
+  };
+  step(std::integral_constant<int, kXor1>{});
+  step(std::integral_constant<int, kXor2>{});
+  step(std::integral_constant<int, kMirror8>{});
+  step(std::integral_constant<int, kMirror16>{});
+#pragma unroll
+  for (int half = 0; half < 2; ++half) {  // lanes 16, then 32 apart: a swap yields both values
+    const Words a = __builtin_bit_cast(Words, v);
+    Words x, y;
+#pragma unroll
+    for (int i = 0; i < W; ++i) {
+      const auto r = half == 0 ? __builtin_amdgcn_permlane16_swap(a.w[i], a.w[i], false, false)
+                               : __builtin_amdgcn_permlane32_swap(a.w[i], a.w[i], false, false);
+      x.w[i] = r[0];
+      y.w[i] = r[1];
+    }
+    v = op(__builtin_bit_cast(T, x), __builtin_bit_cast(T, y));
   }
   return v;
+}
+__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
+  return wave_reduce(v, [](uint32_t a, uint32_t b) { return a > b ? a : b; });
 }
 
 // Per-token quantization parameters derived from the row's max |x|.

@@ -36,22 +36,19 @@ __global__ __launch_bounds__(T) void quantize_rows_block(const uint16_t* __restr
   for (int j = 0; j < C; ++j) m = absmax_chunk(m, cache[j]);
   for (int c = tid + C * T; c < nchunk; c += T) m = absmax_chunk(m, xr[c]);
 
+  // Every thread forms the scale itself from the waves' maxima: one barrier,
+  // and no second trip through LDS.
   __shared__ uint32_t red[T / 64];
-  __shared__ QScale qs;
   m = wave_max_u32(fold_pair_max(m));
   if ((tid & 63) == 0) red[tid >> 6] = m;
-  __syncthreads();
-  if (tid == 0) {
-    uint32_t a = red[0];
+  lds_barrier();
+  uint32_t a = red[0];
 #pragma unroll
-    for (int w = 1; w < T / 64; ++w) a = a > red[w] ? a : red[w];
-    qs = qscale_from_absmax(bf16_lo(a));
-    scale[row] = qs.s;
-  }
-  __syncthreads();
-  const float s = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(qs.s)));
-  const float inv = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(qs.inv)));
+  for (int w = 1; w < T / 64; ++w) a = a > red[w] ? a : red[w];
+  const QScale qs = qscale_from_absmax(bf16_lo(__builtin_amdgcn_readfirstlane(a)));
+  const float s = qs.s, inv = qs.inv;
   const int mode = __builtin_amdgcn_readfirstlane(qs.mode);
+  if (tid == 0) scale[row] = s;
 
 #pragma unroll
   for (int j = 0; j < C; ++j) {
@@ -109,9 +106,12 @@ __global__ __launch_bounds__(kWaveThreads) void quantize_rows_wave(const uint16_
 //   ss = sum_k x_k^2 in fp64 (every square exact; a fixed reduction tree),
 //   v = fl32(ss / K), r = 1 / sqrt(v + eps) (IEEE fp32 operations),
 //   h_k = (x_k * r) * gamma_k in fp32,
-// then the per-token quantize of the fp32 h with IEEE division.  One
-// workgroup of T threads per row, chunks t + T j (j < C) of x and gamma
-// held in registers between the passes.
+// then the per-token quantize of the fp32 h, with the codes of IEEE
+// division.  One workgroup of T threads per row, chunks t + T j (j < C) of x
+// and gamma held in registers between the passes.  With few rows the call is
+// one chain of latencies, so every thread folds the waves' results and forms
+// r and the scale itself (one barrier each), and the waves reduce without
+// LDS; with many the divisions were a third of the vector work.
 template <int T, int C>
 __global__ __launch_bounds__(T) void rmsnorm_quantize_rows(const uint16_t* __restrict__ x,
                                                            const uint16_t* __restrict__ gamma, float eps, int K,
@@ -149,25 +149,20 @@ __global__ __launch_bounds__(T) void rmsnorm_quantize_rows(const uint16_t* __res
 
   __shared__ double red_d[T / 64];
   __shared__ float red_f[T / 64];
-  __shared__ float l_r, l_s;
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) ss += __shfl_xor(ss, off, 64);
+  ss = wave_reduce(ss, [](double a, double b) { return a + b; });
   if ((tid & 63) == 0) red_d[tid >> 6] = ss;
-  __syncthreads();
-  if (tid == 0) {
-    double t = red_d[0];
+  lds_barrier();
+  double t = red_d[0];
 #pragma unroll
-    for (int w = 1; w < T / 64; ++w) t += red_d[w];
-    const float v = (float)(t / (double)K);
-    // The correctly rounded fp32 root, through fp64: the hardware fp32 root
-    // (what the fp32 intrinsic compiles to) is only faithful.  Rounding an
-    // fp64 root within one fp64 ulp to fp32 is exact: the square root of an
-    // fp32 value lies at least 2^-51 (relative) from any fp32 midpoint.
-    const float root = (float)__dsqrt_rn((double)__fadd_rn(v, eps));
-    l_r = __fdiv_rn(1.0f, root);
-  }
-  __syncthreads();
-  const float r = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(l_r)));
+  for (int w = 1; w < T / 64; ++w) t += red_d[w];
+  // ss / K: for a power of two the division is a shift of the exponent
+  const float v = (float)((K & (K - 1)) == 0 ? __builtin_ldexp(t, -__builtin_ctz(K)) : t / (double)K);
+  // The correctly rounded fp32 root, through fp64: the hardware fp32 root
+  // (what the fp32 intrinsic compiles to) is only faithful.  Rounding an
+  // fp64 root within one fp64 ulp to fp32 is exact: the square root of an
+  // fp32 value lies at least 2^-51 (relative) from any fp32 midpoint.
+  const float root = (float)__dsqrt_rn((double)__fadd_rn(v, eps));
+  const float r = __fdiv_rn(1.0f, root);
 
   // h for one chunk of x and gamma (8 values), and the running max of |h|
   auto h_of = [&](const uint4& xv, const uint4& gv, float (&h)[8]) {
@@ -187,30 +182,43 @@ __global__ __launch_bounds__(T) void rmsnorm_quantize_rows(const uint16_t* __res
 #pragma unroll
   for (int j = 0; j < C; ++j) max_of(xc[j], gc[j]);
   for (int c = tid + C * T; c < nchunk; c += T) max_of(xr[c], gr[c]);
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
+  m = wave_reduce(m, [](float a, float b) { return fmaxf(a, b); });
   if ((tid & 63) == 0) red_f[tid >> 6] = m;
-  __syncthreads();
-  if (tid == 0) {
-    float a = red_f[0];
+  lds_barrier();
+  float a = red_f[0];
 #pragma unroll
-    for (int w = 1; w < T / 64; ++w) a = fmaxf(a, red_f[w]);
-    l_s = __fdiv_rn(a, 127.0f);
-    scale[row] = l_s;
-  }
-  __syncthreads();
-  const float sc = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(l_s)));
+  for (int w = 1; w < T / 64; ++w) a = fmaxf(a, red_f[w]);
+  const float sc = __fdiv_rn(a, 127.0f);
+  if (tid == 0) scale[row] = sc;
 
-  // codes: round_half_even(h / s) by IEEE division; |h / s| <= 127 (1 +
-  // 2^-24), so adding 1.5 * 2^23 rounds it and leaves the code in the low byte
+  // codes: round_half_even(fl32(h / s)); |h / s| <= 127 (1 + 2^-24), so
+  // adding 1.5 * 2^23 rounds it and leaves the code in the low byte.  The
+  // quotient is p = h (1 / s) corrected by one fma step, within an ulp
+  // (2^-17) of the rounded quotient: the same code unless it lies that close
+  // to a half.  Chunks with a quotient within 2^-12 of a half (about one in
+  // 250 per chunk of 8) and scales that could underflow in the correction
+  // take the IEEE division.
+  const float inv = __fdiv_rn(1.0f, sc);
+  const bool quick = sc > 0x1p-60f && sc < 0x1p60f;
   auto codes = [&](const uint4& xv, const uint4& gv) {
     float h[8];
     h_of(xv, gv, h);
     uint32_t b[8];
+    bool near = !quick;
 #pragma unroll
-    for (int e = 0; e < 8; ++e)
-      b[e] = sc == 0.0f ? 0u : (__float_as_uint(__fadd_rn(__fdiv_rn(h[e], sc), 12582912.0f)) & 0xFFu);
-    return make_uint2(b[0] | (b[1] << 8) | (b[2] << 16) | (b[3] << 24), b[4] | (b[5] << 8) | (b[6] << 16) | (b[7] << 24));
+    for (int e = 0; e < 8; ++e) {
+      const float p = __fmul_rn(h[e], inv);
+      const float q = __fmaf_rn(__fmaf_rn(-sc, p, h[e]), inv, p);
+      const float n = __fadd_rn(q, 12582912.0f);
+      near |= !(fabsf(q - (n - 12582912.0f)) < 0.5f - 0x1p-12f);
+      b[e] = __float_as_uint(n);
+    }
+    if (near) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e)
+        b[e] = sc == 0.0f ? 0u : __float_as_uint(__fadd_rn(__fdiv_rn(h[e], sc), 12582912.0f));
+    }
+    return make_uint2(pack4(b[0], b[1], b[2], b[3]), pack4(b[4], b[5], b[6], b[7]));
   };
 #pragma unroll
   for (int j = 0; j < C; ++j) {

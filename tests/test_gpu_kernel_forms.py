@@ -39,3 +39,21 @@ def test_rows_of_codes(M, group):
         x = I.activations(M, K, 860 + M)
         W, s = I.weights(N, K, 861 + N, group=group)
         check_all_outputs(x, W, s, group=group, label="rows of codes")
+
+
+# The norm's codes come from a corrected reciprocal product, near halves from
+# IEEE division: enough values (3 M) that ~700 quotients lie within 2^-12 of a
+# half, and gains small and large enough for the scales that always divide.
+@pytest.mark.gpu
+@pytest.mark.parametrize("gain", [1.0, 2.0 ** -70, 2.0 ** 70])
+def test_norm_codes_near_halves(gain):
+    import oracle
+    import torch
+    from helpers import bf16_dev
+    M, K = (256, 12288) if gain == 1.0 else (8, 1152)
+    x = I.activations(M, K, 870)
+    g = I.to_bf16_bits((gain * (1 + 0.1 * np.random.Generator(np.random.PCG64(871)).standard_normal(K))).astype(np.float32))
+    q, s = w.w4a8_rmsnorm_quantize_act(bf16_dev(x), bf16_dev(g), 1e-6)
+    rq, rs = oracle.rmsnorm_quantize(x, g, 1e-6)[:2]
+    np.testing.assert_array_equal(s.cpu().numpy().view(np.uint32), np.asarray(rs, np.float32).view(np.uint32))
+    np.testing.assert_array_equal(q.cpu().numpy(), rq)
