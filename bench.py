@@ -774,7 +774,7 @@ def _short_kernel(full: str) -> str:
 
 def _is_gemm(kernel: str) -> bool:
     k = _short_kernel(kernel)
-    return k.startswith("smallm<") or k.startswith("largem<")
+    return k.startswith("smallm<") or k.startswith("largem")
 
 
 def _per_dispatch(rows, counter: str):
