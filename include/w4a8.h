@@ -181,7 +181,7 @@ w4a8_status w4a8_rmsnorm_quantize_act(const uint16_t* x, const uint16_t* gamma, 
  *   D            128 (W4A8_EUNSUPPORTED otherwise)
  *   H, Hkv       1 <= Hkv, H % Hkv == 0
  *   Nq, Nk       0 <= Nq (0 is a no-op), 1 <= Nk; both <= 2^22
- *   scale        finite (e.g. 1/sqrt(D))
+ *   scale        finite, of either sign or 0 (e.g. 1/sqrt(D))
  *   o            device, bf16 [H][Nq][D], 16-byte aligned
  *   workspace    device, >= w4a8_stream_attention_workspace_bytes(H, Nq, Nk)
  *                bytes, 256-byte aligned: the keys rotated at their

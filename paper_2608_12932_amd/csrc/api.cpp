@@ -4,6 +4,7 @@
 // call has no effect and touches no HIP state.
 #include "w4a8.h"
 
+#include <cmath>
 #include <cstdio>
 #include <mutex>
 
@@ -324,7 +325,10 @@ w4a8_status w4a8_stream_attention(const uint16_t* q, const uint16_t* k, const ui
   a.Nq = (int)Nq;
   a.Nk = (int)Nk;
   a.n_pos = (int)n_pos;
-  a.scale_log2e = scale * 1.4426950408889634f;
+  // The kernel masks raw scores with -inf and scales them afterwards, which
+  // takes a positive factor: the queries carry the scale's sign, or its zero.
+  a.scale_log2e = (scale == 0.0f ? 1.0f : std::fabs(scale)) * 1.4426950408889634f;
+  a.q_sign = scale == 0.0f ? 0.0f : scale < 0.0f ? -1.0f : 1.0f;
   return launch_stream_attention(a, stream) == hipSuccess ? W4A8_OK : W4A8_EHIP;
 }
 

@@ -18,7 +18,8 @@ struct AttnArgs {
   const float* rope_sin;  // [n_pos][64]
   uint16_t* o;            // bf16 [H][Nq][128]
   int H, Hkv, Nq, Nk, n_pos;
-  float scale_log2e;      // score scale times log2(e)
+  float scale_log2e;      // |score scale| times log2(e); positive (log2(e) for a scale of 0)
+  float q_sign;           // the scale's sign, 0 for a scale of 0, applied to the queries
   void* workspace;        // rotated keys and split partials (stream_attention_workspace bytes)
   // set by the launcher
   uint16_t* k_rot;        // bf16 [Hkv][Nk][128]: the keys rotated at their positions

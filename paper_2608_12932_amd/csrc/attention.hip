@@ -448,11 +448,18 @@ __global__ __launch_bounds__(kAttnWaves * 64, 2) void stream_attention(const Att
 #pragma unroll
   for (int n = 0; n < kLoads; ++n) issue_keys(0, n, tile_off(0, cur));
 
+  // (the scale's sign goes into the rotation's factors: 1 and -1 are exact,
+  // and with 0 every score of finite operands is 0)
   bf16x8_t qf[8];
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    const float cs[8] = {rc[i][0].x, rc[i][0].y, rc[i][0].z, rc[i][0].w, rc[i][1].x, rc[i][1].y, rc[i][1].z, rc[i][1].w};
-    const float sn[8] = {rs[i][0].x, rs[i][0].y, rs[i][0].z, rs[i][0].w, rs[i][1].x, rs[i][1].y, rs[i][1].z, rs[i][1].w};
+    float cs[8] = {rc[i][0].x, rc[i][0].y, rc[i][0].z, rc[i][0].w, rc[i][1].x, rc[i][1].y, rc[i][1].z, rc[i][1].w};
+    float sn[8] = {rs[i][0].x, rs[i][0].y, rs[i][0].z, rs[i][0].w, rs[i][1].x, rs[i][1].y, rs[i][1].z, rs[i][1].w};
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      cs[e] *= a.q_sign;
+      sn[e] *= a.q_sign;
+    }
     uint4 lo, hi4;
     rotate_chunks(qraw[i][0], qraw[i][1], cs, sn, lo, hi4);
     qf[i] = as_bf16x8(lo);
@@ -547,8 +554,8 @@ __global__ __launch_bounds__(kAttnWaves * 64, 2) void stream_attention(const Att
       issue_pos(b ^ 1, v_off);
     }
     // ---- online softmax over this lane's query (its 16 keys here, the
-    // other 16 in lane ^ 32), in scaled base-2 units: the scale is
-    // positive, so the largest raw score gives the largest scaled one
+    // other 16 in lane ^ 32), in scaled base-2 units: sl2 is positive, so
+    // the largest raw score gives the largest scaled one and -inf stays -inf
     const float top = max_xor32(tmax) * sl2;
     if (__any(top > m)) {
       const float mnew = fmaxf(m, top);

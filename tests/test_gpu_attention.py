@@ -44,7 +44,7 @@ def run(q, k, v, pos_q, pos_k, cos_t, sin_t, scale):
     return (o.view(torch.int16).cpu().numpy().view(np.uint16).astype(np.uint32) << 16).view(np.float32).astype(np.float64)
 
 
-def check(H, Hkv, pos_q, pos_k, seed, label, rows=None):
+def check(H, Hkv, pos_q, pos_k, seed, label, rows=None, scale=1.0 / np.sqrt(D)):
     Nq, Nk = len(pos_q), len(pos_k)
     print(f"[case] stream attention {label} H={H} Hkv={Hkv} Nq={Nq} Nk={Nk}", flush=True)
     q = I.activations(H * Nq, D, seed).reshape(H, Nq, D)
@@ -52,13 +52,12 @@ def check(H, Hkv, pos_q, pos_k, seed, label, rows=None):
     v = I.activations(Hkv * Nk, D, seed + 2).reshape(Hkv, Nk, D)
     n_pos = int(max(pos_q.max(), pos_k.max())) + 1
     cos_t, sin_t = oracle.rope_tables(n_pos, D, base=1e6)
-    scale = 1.0 / np.sqrt(D)
     o = run(q, k, v, pos_q, pos_k, cos_t, sin_t, scale)
     sel = np.arange(Nq) if rows is None else rows
     o64, bnd = oracle.streaming_attention(q[:, sel], k, v, pos_q[sel], pos_k, cos_t, sin_t, np.float32(scale))
     err = np.abs(o[:, sel] - o64)
     bound = 2.0 ** -8 * np.abs(o64) + 2.0 ** -8 * bnd + 1e-30
-    bad = err > bound
+    bad = ~(err <= bound)  # a NaN is outside it too
     assert not bad.any(), f"{label}: {bad.sum()} outputs outside tolerance, worst ratio {np.max(err / bound):.2f}"
     return float(np.max(err / bound))
 
@@ -258,3 +257,16 @@ def test_running_maximum_moves(steps):
     o = run(q, k, v, pos_q, pos_k, cos_t, sin_t, float(scale))
     o64, bnd = oracle.streaming_attention(q, k, v, pos_q, pos_k, cos_t, sin_t, scale)
     assert (np.abs(o - o64) <= 2.0 ** -8 * np.abs(o64) + 2.0 ** -8 * bnd + 1e-30).all()
+
+
+# Any finite scale is accepted.  Every key visible: one tile, two and three
+# (the last two-tile stage full or half empty), a partial tile; a masked
+# window; key-range splits.
+@pytest.mark.parametrize("scale", [-1.0 / np.sqrt(D), 0.0, -0.0, 1e-30, -1e-45])
+def test_scale_of_any_sign(scale):
+    for Nk in (32, 64, 96, 50):
+        check(2, 1, np.full(70, Nk, np.int32), np.arange(Nk, dtype=np.int32), 840 + Nk, f"scale {scale} Nk={Nk}",
+              scale=scale)
+    for V, F, T in ((2, 3, 40), (1, 3, 32), (4, 4, 125)):
+        pos_k, pos_q = window(V, F, T, 1)
+        check(2, 1, pos_q, pos_k, 850 + T, f"scale {scale} window {V}x{F}x{T}", scale=scale)
