@@ -356,7 +356,8 @@ __global__ __launch_bounds__(kAttnWaves * 64, 2) void stream_attention(const Att
   // of those that some query of the block sees (a tile whose smallest key
   // position lies above the largest query position is left out); bits 0-8
   // the tile within the split, bit 9 + q: every key of it is seen by every
-  // query of half q
+  // query of half q (never of the tile that the cache ends in: the keys past
+  // Nk have the largest position, which a query may have too)
   const bool listed = t_end - t_begin <= kMaxSkipTiles;
   uint16_t* list = reinterpret_cast<uint16_t*>(lds + kLdsList);
   {
@@ -381,9 +382,10 @@ __global__ __launch_bounds__(kAttnWaves * 64, 2) void stream_attention(const Att
       const int2 bd = t0 == t_begin ? bounds0 : a.tile_bounds[min(t, ntiles_all - 1)];
       const bool vis = t < t_end && bd.x <= wg_qmax;
       const uint64_t m = __ballot(vis);
+      const bool whole = (t + 1) * kKeys <= a.Nk;
       if (vis && wave == ((t0 - t_begin) >> 6) % kAttnWaves)
         list[n_vis + __popcll(m & ((1ull << lane) - 1))] =
-            (uint16_t)((t - t_begin) | (bd.y <= qmin0 ? 512 : 0) | (bd.y <= qmin1 ? 1024 : 0));
+            (uint16_t)((t - t_begin) | (whole && bd.y <= qmin0 ? 512 : 0) | (whole && bd.y <= qmin1 ? 1024 : 0));
       n_vis += (int)__popcll(m);
     }
     n_vis = __builtin_amdgcn_readfirstlane(n_vis);

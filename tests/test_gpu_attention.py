@@ -270,3 +270,21 @@ def test_scale_of_any_sign(scale):
     for V, F, T in ((2, 3, 40), (1, 3, 32), (4, 4, 125)):
         pos_k, pos_q = window(V, F, T, 1)
         check(2, 1, pos_q, pos_k, 850 + T, f"scale {scale} window {V}x{F}x{T}", scale=scale)
+
+
+def test_positions_at_the_type_limits():
+    # queries at the largest position see every key, of a partial last tile
+    # too, and nothing past the cache; keys at the smallest are seen by all
+    # (positions outside the table take its ends)
+    H, Hkv, Nq, Nk = 2, 1, 64, 40
+    q = I.activations(H * Nq, D, 860).reshape(H, Nq, D)
+    k = I.activations(Hkv * Nk, D, 861).reshape(Hkv, Nk, D)
+    v = I.activations(Hkv * Nk, D, 862).reshape(Hkv, Nk, D)
+    cos_t, sin_t = oracle.rope_tables(64, D, base=1e6)
+    scale, last, first = np.float32(1.0 / np.sqrt(D)), np.iinfo(np.int32).max, np.iinfo(np.int32).min
+    pos_k = np.arange(Nk, dtype=np.int32)
+    pos_k[:5] = first
+    print("[case] positions at the type limits", flush=True)
+    o = run(q, k, v, np.full(Nq, last, np.int32), pos_k, cos_t, sin_t, float(scale))
+    o64, bnd = oracle.streaming_attention(q, k, v, np.full(Nq, 63), np.maximum(pos_k, 0), cos_t, sin_t, scale)
+    assert (np.abs(o - o64) <= 2.0 ** -8 * np.abs(o64) + 2.0 ** -8 * bnd + 1e-30).all()
