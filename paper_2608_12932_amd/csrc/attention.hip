@@ -313,9 +313,7 @@ __global__ __launch_bounds__(kAttnWaves * 64, 2) void stream_attention(const Att
   const int P = a.n_pos;
   auto clamp_pos = [&](int p) { return p < 0 ? 0 : (p >= P ? P - 1 : p); };  // table reads stay in bounds
 
-  // ---- this lane's query: rotated, as the B operand of S^T = K Q^T
-  // (lane: query l32, d = 16 i + 8 hi .. for MFMA i; chunks i and i + 4 are
-  // a rotate-half pair)
+  // ---- this lane's query
   const int qi = xb * kQPerBlock + qh * kQPerWave + l32;
   const bool q_ok = qi < a.Nq;
   // Everything that the item alone decides is requested at once: the query's
@@ -325,32 +323,30 @@ __global__ __launch_bounds__(kAttnWaves * 64, 2) void stream_attention(const Att
   const int t_begin = split * a.tiles_per_split;
   const int t_end = min(ntiles_all, t_begin + a.tiles_per_split);
   const int2 bounds0 = a.tile_bounds[min(t_begin + lane, ntiles_all - 1)];
-  // Rows past Nq and keys past Nk are out-of-range buffer offsets, which
-  // read zeros.
+  // The workgroup rotates its 64 queries once, 4 threads to a query, the
+  // pairs of chunks (8 p, 64 + 8 p), p = c and c + 4, to thread c, and hands
+  // them round through LDS: loaded by each wave as its operands, the table
+  // rows and queries took twice the loads, each over 32 rows.  Rows past Nq
+  // and keys past Nk are out-of-range buffer offsets, which read zeros.
   const __amdgpu_buffer_rsrc_t qres = make_rsrc(a.q + (size_t)h * a.Nq * kD, (uint32_t)((size_t)a.Nq * kD * 2));
-  uint4 qraw[4][2];  // chunks (16 i + 8 hi, + 64), rotated once the block is known to see a key
-  {
-    const uint32_t qoff = q_ok ? (uint32_t)(qi * kD * 2) : kOOB;
+  const int rq = tid >> 2, rch = tid & 3;  // this thread's row and chunk in the rotation
+  const int rqi = xb * kQPerBlock + rq;
+  const int rpos = rqi < a.Nq ? clamp_pos(a.pos_q[rqi]) : 0;
+  uint4 qraw[2][2];  // rotated once the block is known to see a key
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int d = 16 * i + 8 * hi;  // < 64
-      qraw[i][0] = buf_load16(qres, qoff == kOOB ? kOOB : qoff + d * 2);
-      qraw[i][1] = buf_load16(qres, qoff == kOOB ? kOOB : qoff + (d + kHalf) * 2);
+  for (int u = 0; u < 2; ++u)
+#pragma unroll
+    for (int e = 0; e < 2; ++e)
+      qraw[u][e] = buf_load16(qres, rqi < a.Nq ? (uint32_t)((rqi * kD + 8 * (rch + 4 * u) + kHalf * e) * 2) : kOOB);
+  float4 rc[2][2], rs[2][2];  // the table row (requested before the list is made)
+#pragma unroll
+  for (int u = 0; u < 2; ++u)
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      const size_t at = (size_t)rpos * kHalf + 8 * (rch + 4 * u) + 4 * e;
+      rc[u][e] = *reinterpret_cast<const float4*>(a.rope_cos + at);
+      rs[u][e] = *reinterpret_cast<const float4*>(a.rope_sin + at);
     }
-  }
-
-  // the rotary table row of the query (requested before the list is made)
-  float4 rc[4][2], rs[4][2];
-  {
-    const int pc = clamp_pos(q_ok ? pq : 0);
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        rc[i][u] = *reinterpret_cast<const float4*>(a.rope_cos + (size_t)pc * kHalf + 16 * i + 8 * hi + 4 * u);
-        rs[i][u] = *reinterpret_cast<const float4*>(a.rope_sin + (size_t)pc * kHalf + 16 * i + 8 * hi + 4 * u);
-      }
-  }
 
   // ---- this workgroup's key tiles (its split of the key range): the list
   // of those that some query of the block sees (a tile whose smallest key
@@ -450,24 +446,31 @@ __global__ __launch_bounds__(kAttnWaves * 64, 2) void stream_attention(const Att
 #pragma unroll
   for (int n = 0; n < kLoads; ++n) issue_keys(0, n, tile_off(0, cur));
 
-  // (the scale's sign goes into the rotation's factors: 1 and -1 are exact,
-  // and with 0 every score of finite operands is 0)
-  bf16x8_t qf[8];
+  // The rotated queries, laid out as two tiles of keys, where the second
+  // stage's values come later (the scale's sign goes into the rotation's
+  // factors: 1 and -1 are exact, and with 0 every score of finite operands
+  // is 0).
+  uint8_t* l_q = lds + kLdsV + kStageKV;
+  static_assert(kQPerBlock * kD * 2 <= kStageKV, "the queries fit a stage's values");
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    float cs[8] = {rc[i][0].x, rc[i][0].y, rc[i][0].z, rc[i][0].w, rc[i][1].x, rc[i][1].y, rc[i][1].z, rc[i][1].w};
-    float sn[8] = {rs[i][0].x, rs[i][0].y, rs[i][0].z, rs[i][0].w, rs[i][1].x, rs[i][1].y, rs[i][1].z, rs[i][1].w};
+  for (int u = 0; u < 2; ++u) {
+    float cs[8] = {rc[u][0].x, rc[u][0].y, rc[u][0].z, rc[u][0].w, rc[u][1].x, rc[u][1].y, rc[u][1].z, rc[u][1].w};
+    float sn[8] = {rs[u][0].x, rs[u][0].y, rs[u][0].z, rs[u][0].w, rs[u][1].x, rs[u][1].y, rs[u][1].z, rs[u][1].w};
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
       cs[e] *= a.q_sign;
       sn[e] *= a.q_sign;
     }
     uint4 lo, hi4;
-    rotate_chunks(qraw[i][0], qraw[i][1], cs, sn, lo, hi4);
-    qf[i] = as_bf16x8(lo);
-    qf[i + 4] = as_bf16x8(hi4);
+    rotate_chunks(qraw[u][0], qraw[u][1], cs, sn, lo, hi4);
+    const int ch = rch + 4 * u, sw = rq & 15;
+    *reinterpret_cast<uint4*>(l_q + rq * 256 + ((ch ^ sw) << 4)) = lo;
+    *reinterpret_cast<uint4*>(l_q + rq * 256 + (((ch + 8) ^ sw) << 4)) = hi4;
   }
 
+  // This lane's query as the B operand of S^T = K Q^T (query l32,
+  // d = 16 i + 8 hi .. for MFMA i), read behind the first keys' barrier.
+  bf16x8_t qf[8];
   f32x16_t acc[kD / 32];
 #pragma unroll
   for (int t = 0; t < kD / 32; ++t)
@@ -654,7 +657,10 @@ __global__ __launch_bounds__(kAttnWaves * 64, 2) void stream_attention(const Att
     constexpr std::integral_constant<int, 1> b1{};
     f32x16_t s0, s1;
     wait_vmcnt<0>();
-    lds_barrier();
+    lds_barrier();  // the first keys and the queries are there
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      qf[i] = as_bf16x8(*reinterpret_cast<const uint4*>(l_q + (qh * kQPerWave + l32) * 256 + (((2 * i + hi) ^ (l32 & 15)) << 4)));
 #pragma unroll
     for (int n = 0; n < kLoads; ++n) {
       issue_values(0, n, tile_off(0, cur));
