@@ -798,9 +798,14 @@ int used_splits(int H, int Nq, int Nk, int* tiles_per_split) {
   if (tiles_per_split) *tiles_per_split = tps;
   return (ntiles + tps - 1) / tps;
 }
-// Bytes of the dispatch schedule (0 for calls past its limits).
+// Bytes of the dispatch schedule (0 for calls without one: those past its
+// limits, and those of at most one workgroup per CU, whose order cannot
+// matter: making it is the longest chain of the first kernel, and reading it
+// the first of the second.  us a call with / without: 1 x 2 x 16 on 8 heads
+// 10.5 / 8.7, 2 x 2 x 40 on 16 13.5 / 11.7, 1 x 2 x 256 on 16 19.2 / 17.1).
 size_t schedule_bytes(int H, int Nq, int Nk) {
   const long classes = (long)((Nq + kQPerBlock - 1) / kQPerBlock) * used_splits(H, Nq, Nk, nullptr);
+  if (classes * H <= 256) return 0;
   if (classes > kSchedMaxClasses || (Nk + kKeys - 1) / kKeys > kSchedMaxTiles) return 0;
   const size_t blocks = (size_t)(Nq + kQPerBlock - 1) / kQPerBlock;
   return (((size_t)classes * H + blocks) * sizeof(int) + 255) / 256 * 256;  // the schedule, then the solo table
