@@ -33,6 +33,7 @@
 //     comes out of LDS in the same key order through transposing reads.
 // Rotations are fp32 IEEE operations rounded to bf16, as a bf16 model holds
 // its rotated operands.
+#include <algorithm>
 #include <climits>
 #include <type_traits>
 
@@ -95,8 +96,9 @@ constexpr int kSchedMaxTiles = 1024;   // 32-key tiles
 
 // The order in which the attention's workgroups take their work items.
 // Workgroup ids are dealt to the CUs in rounds of C consecutive ids (id mod
-// C picks the CU while every workgroup is resident), so a CU runs one item
-// of each round side by side.  The items are ranked by their number of
+// C picks the CU in the first two rounds, which are resident together), so a
+// CU runs one item of each side by side; later ids go where a workgroup has
+// ended.  The items are ranked by their number of
 // visible key tiles (the same for every head of a (query block, split)
 // pair) and dealt heaviest first, every second round in reverse: a CU that
 // gets one of the heaviest items of a round gets one of the lightest of the
@@ -770,19 +772,32 @@ __global__ __launch_bounds__(256) void attn_combine(const AttnArgs a) {
 
 }  // namespace
 
-// Key-range splits (at most 8, at least 8 tiles each): the heaviest
-// workgroups, whose queries see the whole window, otherwise run every tile
-// in series.
+// Key-range splits (1, 2, 4 or 8, of at least 6 tiles): the heaviest workgroups, whose queries see
+// the whole window, otherwise run every tile in series; each split costs a
+// prologue and its partial sums' way through memory.  The least of, in ns,
+//   the longer of 400 a tile of the heaviest workgroup and 1 a tile of all
+//   (256 CUs, the two workgroups that fit one, ~60 % of the keys visible),
+//   and with splits 1000 for the merge and 20 a workgroup.
+// Fitted to S = 1, 2, 4, 8 of 80 windows (1 - 6 views, 2 - 6 frames, 16 - 256
+// tokens, 8 - 32 heads): 0.8 % above the best S on average, 8 % at most.
+// (Splitting up to 4 workgroups a CU, as when that many fitted, took 8 %
+// more.)  us at S = 1, 2, 4, 8: 4 x 4 x 192 on 32 heads (384 blocks, 96
+// tiles) 51.8 54.2 61.0 80.1; 2 x 4 x 192 on 32 (192, 48) 30.5 31.2 37.5
+// 45.8; 4 x 6 x 128 on 32 (256, 96) 54.8 42.4 51.5 59.8; 4 x 4 x 192 on 8
+// (96, 96) 48.1 35.5 31.6 35.9; 1 x 16 x 256 on 8 (32, 128) 65.0 42.8 31.4
+// 28.6.
 int stream_attention_splits(int H, int Nq, int Nk) {
-  const long blocks = (long)((Nq + kQPerBlock - 1) / kQPerBlock) * H;
-  const int ntiles = (Nk + kKeys - 1) / kKeys;
-  // split until the grid would outgrow one round of resident workgroups
-  // (4 per CU at 128 registers per lane, on 256 CUs): a second round costs
-  // more than the longer serial key loop it saves
-  constexpr long kResident = 4 * 256;
-  int S = 1;
-  while (S < 8 && blocks * S * 2 <= kResident && ntiles / (S * 2) >= 8) S *= 2;
-  return S;
+  const int64_t blocks = (int64_t)((Nq + kQPerBlock - 1) / kQPerBlock) * H, ntiles = (Nk + kKeys - 1) / kKeys;
+  int best = 1;
+  int64_t least = INT64_MAX;
+  for (int S = 1; S <= 8 && (S == 1 || ntiles / S >= 6); S *= 2) {
+    const int64_t cost = std::max(400 * ntiles / S, blocks * ntiles) + (S > 1 ? 1000 + 20 * blocks * S : 0);
+    if (cost < least) {
+      least = cost;
+      best = S;
+    }
+  }
+  return best;
 }
 
 // Workspace, past the counter region shared with the linear calls'

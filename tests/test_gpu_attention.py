@@ -36,6 +36,16 @@ def window(V, F, T, shift):
     return pos_k, pos_q
 
 
+def workspace(H, Nq, Nk, S, scheduled):
+    """The workspace of a call with S key-range splits: 64 KiB, the rotated
+    keys (H x Nk x 128 bf16), the tile bounds, the schedule with the solo
+    table, the partial sums."""
+    X, ntiles = (Nq + 63) // 64, (Nk + 31) // 32
+    up = lambda n: (n + 255) // 256 * 256
+    return (64 * 1024 + up(H * Nk * 128 * 2) + up(ntiles * 8) + (up((X * S * H + X) * 4) if scheduled else 0) +
+            (S * H * Nq * 130 * 4 if S > 1 else 0))
+
+
 def run(q, k, v, pos_q, pos_k, cos_t, sin_t, scale):
     t = lambda a: torch.from_numpy(np.ascontiguousarray(a).view(np.int16)).to(dev()).view(torch.bfloat16)
     o = w.w4a8_stream_attention(t(q), t(k), t(v), torch.from_numpy(pos_q).to(dev()), torch.from_numpy(pos_k).to(dev()),
@@ -111,14 +121,16 @@ def test_lone_split_past_the_first():
     check(2, 1, pos_q, pos_k, 813, "lone split 7 of 8")
 
 
-@pytest.mark.parametrize("H,Hkv,Nq", [(4, 2, 4096), (2, 1, 10240)])
-def test_schedule_limit(H, Hkv, Nq):
-    # 4096 keys in position order under Nq queries spread over them: 4 query
-    # heads x 4096 queries give 64 query blocks x 4 splits = 256 (block,
-    # split) pairs, the most the dispatch schedule deals (1024 workgroups);
-    # 2 heads x 10240 queries give 160 x 2 = 320 pairs, past it, so the plain
-    # grid with a merge runs (64 sampled queries each)
-    Nk = 4096
+@pytest.mark.parametrize("H,Hkv,Nq,Nk,S,scheduled", [(2, 1, 8192, 4096, 2, True), (1, 1, 12800, 4096, 2, False),
+                                                        (32, 8, 512, 128, 1, False), (36, 4, 512, 128, 1, True)])
+def test_schedule_limit(H, Hkv, Nq, Nk, S, scheduled):
+    # Nk keys in position order under Nq queries spread over them: 2 query
+    # heads x 8192 queries give 128 query blocks x 2 splits = 256 (block,
+    # split) pairs, the most the dispatch schedule deals; 12800 queries give
+    # 200 x 2 = 400 pairs, past it, so the plain grid with a merge runs; 32
+    # heads x 512 queries give 256 workgroups, one a CU, which need no
+    # schedule; 36 heads give 288, which have one (64 sampled queries each)
+    assert w.w4a8_stream_attention_workspace_bytes(H, Nq, Nk) == workspace(H, Nq, Nk, S, scheduled)
     pos_k = np.arange(Nk, dtype=np.int32)
     pos_q = np.sort(np.random.Generator(np.random.PCG64(814)).integers(0, Nk, Nq)).astype(np.int32)
     rows = np.sort(np.random.Generator(np.random.PCG64(815)).choice(Nq, 64, replace=False))
@@ -142,17 +154,13 @@ def test_query_seeing_no_key_gets_zero():
 
 def test_long_cache_without_tile_skipping():
     # 10 frames x 4096 tokens of one view (40960 keys) under 4096 queries: so
-    # many query blocks that the key range splits in 2 only, with more tiles
-    # per split than the skip table holds, so every tile is computed and
+    # many query blocks that the key range is not split, with more tiles
+    # than the list of visible ones holds, so every tile is computed and
     # masked (the path without tile skipping); 64 sampled queries
     pos_k, pos_q = window(1, 10, 4096, 3)
     H, Hkv, Nq, Nk = 8, 2, len(pos_q), len(pos_k)
-    # workspace: 64 KiB, the rotated keys (H * Nk * 128 bf16), the partials
-    rot = (H * Nk * 128 * 2 + 255) // 256 * 256
-    bounds = ((Nk + 31) // 32 * 8 + 255) // 256 * 256
     assert (Nk + 31) // 32 > 1024  # past the dispatch schedule's limit: no schedule bytes
-    S = (w.w4a8_stream_attention_workspace_bytes(H, Nq, Nk) - 64 * 1024 - rot - bounds) // (H * Nq * 130 * 4)
-    assert S >= 1 and (Nk // 32) / S > 512
+    assert w.w4a8_stream_attention_workspace_bytes(H, Nq, Nk) == workspace(H, Nq, Nk, 1, False)
     rows = np.sort(np.random.Generator(np.random.PCG64(809)).choice(Nq, 64, replace=False))
     check(H, Hkv, pos_q, pos_k, 810, "long cache 1x10x4096", rows=rows)
 
@@ -163,9 +171,10 @@ def test_dispatch_schedule():
     # rounds of one id per CU, every second full round reversed.  Read the
     # schedule back from a caller workspace and compare it with that rule
     # computed here from the positions; it must be a permutation, and the
-    # per-CU tile sums of the 4x4x192 window must stay within 10 % of the
-    # mean (94 against 87; the plain order gives up to 140).
-    V, F, T, H, Hkv = 4, 4, 192, 32, 8
+    # per-CU tile sums of the 4x6x128 window (256 blocks in 2 splits: two
+    # rounds, resident together) must stay within 20 % of the mean (70
+    # against 59; the plain order gives up to 96).
+    V, F, T, H, Hkv = 4, 6, 128, 32, 8
     pos_k, pos_q = window(V, F, T, 1)
     Nq, Nk = len(pos_q), len(pos_k)
     need = w.w4a8_stream_attention_workspace_bytes(H, Nq, Nk)
@@ -178,7 +187,8 @@ def test_dispatch_schedule():
                             torch.from_numpy(cos_t).to(dev()), torch.from_numpy(sin_t).to(dev()), 0.1, workspace=ws)
     torch.cuda.synchronize()
     X, ntiles = (Nq + 63) // 64, (Nk + 31) // 32
-    S = 2  # the split rule's choice here: 384 blocks x 2 fill one resident round
+    S = 2  # the split rule's choice here
+    assert need == workspace(H, Nq, Nk, S, True)
     tps = (ntiles + S - 1) // S
     G = X * S * H
     off = 64 * 1024 + (H * Nk * 128 * 2 + 255) // 256 * 256 + (ntiles * 8 + 255) // 256 * 256
@@ -206,7 +216,7 @@ def test_dispatch_schedule():
         cu = np.zeros(C)
         for i, code in enumerate(sched):
             cu[i % C] += vis[code // H]
-        assert cu.max() <= 1.10 * cu.mean(), (cu.min(), cu.mean(), cu.max())
+        assert cu.max() <= 1.20 * cu.mean(), (cu.min(), cu.mean(), cu.max())
 
 
 def test_rejected_calls():
