@@ -772,7 +772,7 @@ __global__ __launch_bounds__(256) void attn_combine(const AttnArgs a) {
 
 }  // namespace
 
-// Key-range splits (1, 2, 4 or 8, of at least 6 tiles): the heaviest workgroups, whose queries see
+// Key-range splits (1, 2, 4 or 8, of at least 8 tiles): the heaviest workgroups, whose queries see
 // the whole window, otherwise run every tile in series; each split costs a
 // prologue and its partial sums' way through memory.  The least of, in ns,
 //   the longer of 400 a tile of the heaviest workgroup and 1 a tile of all
@@ -790,7 +790,7 @@ int stream_attention_splits(int H, int Nq, int Nk) {
   const int64_t blocks = (int64_t)((Nq + kQPerBlock - 1) / kQPerBlock) * H, ntiles = (Nk + kKeys - 1) / kKeys;
   int best = 1;
   int64_t least = INT64_MAX;
-  for (int S = 1; S <= 8 && (S == 1 || ntiles / S >= 6); S *= 2) {
+  for (int S = 1; S <= 8 && (S == 1 || ntiles / S >= 8); S *= 2) {
     const int64_t cost = std::max(400 * ntiles / S, blocks * ntiles) + (S > 1 ? 1000 + 20 * blocks * S : 0);
     if (cost < least) {
       least = cost;
@@ -813,14 +813,9 @@ int used_splits(int H, int Nq, int Nk, int* tiles_per_split) {
   if (tiles_per_split) *tiles_per_split = tps;
   return (ntiles + tps - 1) / tps;
 }
-// Bytes of the dispatch schedule (0 for calls without one: those past its
-// limits, and those of at most one workgroup per CU, whose order cannot
-// matter: making it is the longest chain of the first kernel, and reading it
-// the first of the second.  us a call with / without: 1 x 2 x 16 on 8 heads
-// 10.5 / 8.7, 2 x 2 x 40 on 16 13.5 / 11.7, 1 x 2 x 256 on 16 19.2 / 17.1).
+// Bytes of the dispatch schedule (0 for calls past its limits).
 size_t schedule_bytes(int H, int Nq, int Nk) {
   const long classes = (long)((Nq + kQPerBlock - 1) / kQPerBlock) * used_splits(H, Nq, Nk, nullptr);
-  if (classes * H <= 256) return 0;
   if (classes > kSchedMaxClasses || (Nk + kKeys - 1) / kKeys > kSchedMaxTiles) return 0;
   const size_t blocks = (size_t)(Nq + kQPerBlock - 1) / kQPerBlock;
   return (((size_t)classes * H + blocks) * sizeof(int) + 255) / 256 * 256;  // the schedule, then the solo table
@@ -853,7 +848,13 @@ hipError_t launch_stream_attention(const AttnArgs& a0, hipStream_t stream) {
   a.k_rot = reinterpret_cast<uint16_t*>(ws);
   a.tile_bounds = reinterpret_cast<int2*>(ws + rotated_keys_bytes(a.H, a.Nk));
   const size_t sched_bytes = schedule_bytes(a.H, a.Nq, a.Nk);
-  a.sched = sched_bytes ? reinterpret_cast<int*>(ws + rotated_keys_bytes(a.H, a.Nk) + tile_bounds_bytes(a.Nk)) : nullptr;
+  // Calls of at most one workgroup per CU go without a schedule: their order
+  // cannot matter, and making it is the longest chain of the first kernel,
+  // reading it the first of the second.  us a call with / without: 1 x 2 x 16
+  // on 8 heads 10.5 / 8.7, 2 x 2 x 40 on 16 13.5 / 11.7, 1 x 2 x 256 on 16
+  // 19.2 / 17.1.
+  const int64_t items = (int64_t)((a.Nq + kQPerBlock - 1) / kQPerBlock) * a.S * a.H;
+  a.sched = sched_bytes && items > 256 ? reinterpret_cast<int*>(ws + rotated_keys_bytes(a.H, a.Nk) + tile_bounds_bytes(a.Nk)) : nullptr;
   a.sched_cus = compute_units();
   a.solo = a.sched ? a.sched + (size_t)((a.Nq + kQPerBlock - 1) / kQPerBlock) * a.S * a.H : nullptr;
   if (a.S > 1) {

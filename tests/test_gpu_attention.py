@@ -38,8 +38,8 @@ def window(V, F, T, shift):
 
 def workspace(H, Nq, Nk, S, scheduled):
     """The workspace of a call with S key-range splits: 64 KiB, the rotated
-    keys (H x Nk x 128 bf16), the tile bounds, the schedule with the solo
-    table, the partial sums."""
+    keys (H x Nk x 128 bf16), the tile bounds, room for the schedule with
+    the solo table, the partial sums."""
     X, ntiles = (Nq + 63) // 64, (Nk + 31) // 32
     up = lambda n: (n + 255) // 256 * 256
     return (64 * 1024 + up(H * Nk * 128 * 2) + up(ntiles * 8) + (up((X * S * H + X) * 4) if scheduled else 0) +
@@ -89,7 +89,7 @@ def test_streaming_window_realistic_size():
 
 def test_key_range_splits():
     # few query blocks over a long cache: the key range is split over
-    # workgroups and merged (8 splits here; early queries see no key of the
+    # workgroups and merged (4 splits here; early queries see no key of the
     # later splits), with a ragged last tile
     pos_k, pos_q = window(4, 4, 125, 2)
     assert w.w4a8_stream_attention_workspace_bytes(2, len(pos_q), len(pos_k)) > 0
@@ -122,13 +122,13 @@ def test_lone_split_past_the_first():
 
 
 @pytest.mark.parametrize("H,Hkv,Nq,Nk,S,scheduled", [(2, 1, 8192, 4096, 2, True), (1, 1, 12800, 4096, 2, False),
-                                                        (32, 8, 512, 128, 1, False), (36, 4, 512, 128, 1, True)])
+                                                        (32, 8, 512, 128, 1, True), (36, 4, 512, 128, 1, True)])
 def test_schedule_limit(H, Hkv, Nq, Nk, S, scheduled):
     # Nk keys in position order under Nq queries spread over them: 2 query
     # heads x 8192 queries give 128 query blocks x 2 splits = 256 (block,
     # split) pairs, the most the dispatch schedule deals; 12800 queries give
     # 200 x 2 = 400 pairs, past it, so the plain grid with a merge runs; 32
-    # heads x 512 queries give 256 workgroups, one a CU, which need no
+    # heads x 512 queries give 256 workgroups, one a CU, which go without a
     # schedule; 36 heads give 288, which have one (64 sampled queries each)
     assert w.w4a8_stream_attention_workspace_bytes(H, Nq, Nk) == workspace(H, Nq, Nk, S, scheduled)
     pos_k = np.arange(Nk, dtype=np.int32)
