@@ -31,7 +31,6 @@ LargeMKernelFn channel_kernel(int cfg, bool swiglu) {
 // Gated plans (swiglu) take the tiles whose waves hold an even number of
 // blocks (gate and up halves): a tile covers BN / 2 output columns.
 LargeMPlan plan_largem(int M, int N, int K, bool group, bool swiglu) {
-  (void)K;
   LargeMPlan p{};
   p.group = group;
   p.swiglu = swiglu;
@@ -90,14 +89,23 @@ LargeMPlan plan_largem(int M, int N, int K, bool group, bool swiglu) {
     p.threads = 64 * kMenu[p.cfg].GM * kMenu[p.cfg].GN * kMenu[p.cfg].ks;
   }
   const TileCfg& c = kMenu[p.cfg];
-  const int ring = group && p.cfg == 1 ? kGroup128Ring : c.ring;
+  // 128 x 128 group tiles: two workgroups per CU hide each other's latencies
+  // (largem_group128); one alone does better reading its operands a step
+  // ahead (largem_kernel.h), unless K is short and the start and the end
+  // count.  us (paired / ahead), 256 tiles at most: gated, 16 tiles K = 512
+  // 6.8 / 7.1, 1024 9.1 / 9.3, 2048 14.2 / 13.6, 4096 23.8 / 22.3, 12288 61.5
+  // / 56.7; gated, 256 tiles K = 4096 24.3 / 24.2, 12288 68.4 / 66.3; plain,
+  // 224 tiles K = 1024 9.5 / 9.9, 4096 23.9 / 23.8, 8192 42.8 / 41.9, 12288
+  // 61.8 / 60.3.
+  p.paired = group && p.cfg == 1 && (p.tiles > 256 || K < (swiglu ? 2048 : 8192));
+  const int ring = p.paired ? kGroup128Ring : c.ring;
   p.lds_bytes = (size_t)ring * ((size_t)p.BM * 128 + (size_t)p.BN / 16 * kBlockBytes +
                                 (group ? (size_t)(c.GM * c.GN) * 256 : 0));
   return p;
 }
 
 hipError_t launch_largem(const LargeMPlan& p, const LargeMArgs& a, hipStream_t stream) {
-  LargeMKernelFn k = p.group ? largem_group_kernel(p.cfg, p.swiglu) : channel_kernel(p.cfg, p.swiglu);
+  LargeMKernelFn k = p.group ? largem_group_kernel(p.cfg, p.swiglu, p.paired) : channel_kernel(p.cfg, p.swiglu);
   if (!k || p.tiles < 1 || p.tiles > kMaxGrid) return hipErrorInvalidValue;
   const unsigned grid = (unsigned)p.tiles;
   hipLaunchKernelGGL(k, dim3(grid), dim3(p.threads), p.lds_bytes, stream, a);
@@ -106,8 +114,9 @@ hipError_t launch_largem(const LargeMPlan& p, const LargeMArgs& a, hipStream_t s
 
 const char* largem_kernel_name(const LargeMPlan& p) {
   static thread_local char buf[96];
-  snprintf(buf, sizeof buf, "largem<%dx%d,%s%s%s> tiles=%dx%d", p.BM, p.BN, p.group ? "group" : "channel",
-           p.swiglu ? ",swiglu" : "", kMenu[p.cfg].ks > 1 ? ",ksplit" : "", p.tiles_m, p.tiles_n);
+  snprintf(buf, sizeof buf, "largem<%dx%d,%s%s%s%s> tiles=%dx%d", p.BM, p.BN, p.group ? "group" : "channel",
+           p.swiglu ? ",swiglu" : "", kMenu[p.cfg].ks > 1 ? ",ksplit" : "",
+           p.group && p.cfg == 1 && !p.paired ? ",ahead" : "", p.tiles_m, p.tiles_n);
   return buf;
 }
 

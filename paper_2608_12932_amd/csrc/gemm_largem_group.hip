@@ -8,8 +8,9 @@
 // default AGPR form, which is faster for them.
 //
 // The 128 x 128 tile (plain and gated) has a kernel of its own here, held to
-// 256 registers and 75 KiB of LDS so that two workgroups share a CU; the
-// 64 x 64 tiles are instances of largem_kernel.h.
+// 256 registers and 75 KiB of LDS so that two workgroups share a CU; where
+// there is only one per CU it is an instance of largem_kernel.h, like the
+// 64 x 64 tiles.
 #include "largem_kernel.h"
 
 namespace w4a8 {
@@ -290,10 +291,11 @@ __global__ __launch_bounds__(256, 2) void largem_group128(const LargeMArgs a) {
 
 }  // namespace
 
-LargeMKernelFn largem_group_kernel(int cfg, bool swiglu) {
-  if (swiglu) return cfg == 1 ? largem_group128<true> : nullptr;  // the gated tile that fits group mode
+LargeMKernelFn largem_group_kernel(int cfg, bool swiglu, bool paired) {
+  if (swiglu)  // the gated tile that fits group mode
+    return cfg != 1 ? nullptr : paired ? largem_group128<true> : menu_kernel<1, true, true>();
   switch (cfg) {
-    case 1: return largem_group128<false>;
+    case 1: return paired ? largem_group128<false> : menu_kernel<1, true>();
     case 2: return menu_kernel<2, true>();
     case kMenuKSplit: return menu_kernel<kMenuKSplit, true>();
     default: return nullptr;  // 128 x 192 does not fit the group accumulators

@@ -82,6 +82,7 @@ struct LargeMPlan {
   bool swiglu;           // gated output (the 128 x 128 tile; a tile covers BN / 2 output columns)
   int tiles_m, tiles_n;
   int64_t tiles;         // tiles_m * tiles_n, the grid size
+  bool paired;           // 128 x 128 group tile: the kernel of which two workgroups share a CU
   size_t lds_bytes;
 };
 // Largest grid a launch takes (one workgroup per tile).
@@ -91,8 +92,8 @@ hipError_t launch_largem(const LargeMPlan& p, const LargeMArgs& a, hipStream_t s
 typedef void (*LargeMKernelFn)(const LargeMArgs);
 // group-scale instance of tile-menu entry cfg (gemm_largem_group.hip), or
 // nullptr where the tile does not fit the group accumulators (or, gated,
-// for any tile but the gated one)
-LargeMKernelFn largem_group_kernel(int cfg, bool swiglu);
+// for any tile but the gated one); paired: see LargeMPlan
+LargeMKernelFn largem_group_kernel(int cfg, bool swiglu, bool paired);
 
 // ---- flow-matching Euler step with the velocity cache (flow.hip)
 // v == nullptr: a reused step (x += dt * cache); otherwise cache = v after

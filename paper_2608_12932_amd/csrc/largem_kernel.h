@@ -60,7 +60,7 @@ struct TileCfg {
   int WM, WN, GM, GN, ring;
   int ks;          // k groups of GM x GN waves (each with ring / ks stages)
   double quality;  // relative efficiency of the tile shape (operand reuse)
-  bool group_ok;   // has a group-scale form: 64 x 64 here, 128 x 128 as largem_group128
+  bool group_ok;   // fits the registers with group-mode accumulators
   bool plain_ok;   // serves the plain output (its fp32 tile fits the LDS ring)
   bool gated_ok;   // serves the gated output (an even number of blocks per wave)
 };
@@ -82,7 +82,7 @@ constexpr TileCfg kMenu[] = {
 };
 constexpr int kMenuKSplit = 4;  // the k-split form of entry 2
 constexpr int kMenuSize = sizeof(kMenu) / sizeof(kMenu[0]);
-constexpr int kGroup128Ring = 3;  // entry 1 with group scales has its own kernel (gemm_largem_group.hip)
+constexpr int kGroup128Ring = 3;  // entry 1 with group scales also has a kernel of its own (gemm_largem_group.hip)
 
 template <int WM, int WN, int GM, int GN, bool GROUP, int kRing, bool SW, int KS = 1>
 __global__ __launch_bounds__(GM * GN * 64 * KS) void largem(const LargeMArgs a) {
@@ -318,9 +318,10 @@ __global__ __launch_bounds__(GM * GN * 64 * KS) void largem(const LargeMArgs a) 
   if constexpr (!GROUP) load_sx();
 
   // Channel mode accumulates every step into acc[0].  Group mode rescales
-  // each step's int32 partial into facc: the steps alternate between two
-  // accumulator sets so that the rescale of one overlaps the MFMAs of the
-  // next (64 x 64 tiles; the 128 x 128 group tile is largem_group128).
+  // each step's int32 partial into facc: with the 64 x 64 tile the steps
+  // alternate between two accumulator sets so that the rescale of one
+  // overlaps the MFMAs of the next; the 128 x 128 tile uses one set (see
+  // step1 below).
   v16i acc[GROUP ? 2 : 1][WM][WN];
   float facc[GROUP ? WM : 1][GROUP ? WN : 1][16];
 #pragma unroll
@@ -423,6 +424,64 @@ __global__ __launch_bounds__(GM * GN * 64 * KS) void largem(const LargeMArgs a) 
       for (int j = 0; j < WN; ++j) sg_prev[j] = cur.sg[j];
   };
 
+  // Group mode with at least 12 MFMAs per step: one accumulator set.  A
+  // block's four MFMAs run back to back (block t in slots 4t .. 4t + 3, the
+  // first from a zero operand), and its 16 partials are rescaled over the
+  // kW slots from 4t + 5 on; those that fall past the step's last slot are
+  // done early in the next step, before that step's first MFMA into the
+  // block (slot 4t), with the scale of the step they belong to.  The next
+  // step's weights are unpacked whole during this one (k half 0 from 3/16
+  // of the slots on, k half 1 from 10/16, after their LDS reads land).
+  constexpr int kW = kMfma >= 16 ? 8 : kMfma - 5;
+  auto rescale_slot = [&](int q, bool wrapped, const v16i (&c)[WM][WN], const float (&sg)[GROUP ? WN : 1]) {
+#pragma unroll
+    for (int t = 0; t < WM * WN; ++t)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        const int slot = 4 * t + 5 + e * kW / 16;
+        if ((!wrapped && slot == q) || (wrapped && slot - kMfma == q)) {
+          const int i = t / WN, j = t % WN;
+          facc[i][j][e] = __fmaf_rn((float)c[i][j][e], sg[j], facc[i][j][e]);
+        }
+      }
+  };
+  float sg_last[GROUP ? WN : 1];
+#pragma unroll
+  for (int j = 0; j < (GROUP ? WN : 1); ++j) sg_last[j] = 0.0f;
+  auto step1 = [&](auto stage_c, int kb, const Ops& cur, Ops& nxt, v16i (&c)[WM][WN]) {
+    constexpr int S = decltype(stage_c)::value;
+    wait_vmcnt<(kOwnRing - 2) * kPerStage>();
+    lds_barrier();
+#pragma unroll
+    for (int q = 0; q < kMfma; ++q) {
+      const int t = q / 4, sub = q % 4, tp = sub / 2, h = sub % 2, i = t / WN, j = t % WN;
+      rescale_slot(q, true, c, sg_last);  // before this step overwrites the block
+      const v4i& bop = tp == 0 ? (h ? cur.hi0[j] : cur.lo0[j]) : (h ? cur.hi1[j] : cur.lo1[j]);
+      if (sub == 0)
+        c[i][j] = mfma32(cur.a[i][2 * tp + h], bop, v16i{});
+      else
+        c[i][j] = mfma32(cur.a[i][2 * tp + h], bop, c[i][j]);
+#pragma unroll
+      for (int d = 0; d < kPerStage; ++d)
+        if (d * kMfma / kPerStage == q) issue_one(kb + kRing, S, d);
+#pragma unroll
+      for (int r = 0; r < kReads; ++r)
+        if (r * kMfma / kReads == q) read_one(std::integral_constant<int, (S + 1) % kOwnRing>{}, r, nxt);
+#pragma unroll
+      for (int u = 0; u < kUnits; ++u) {
+        if (q == kMfma * 3 / 16 + u * (kMfma * 6 / 16) / kUnits)
+          unpack_word(nxt.b[u / 4][0], u % 4, nxt.lo0[u / 4], nxt.hi0[u / 4]);
+        if (q == kMfma * 10 / 16 + u * (kMfma * 6 / 16) / kUnits)
+          unpack_word(nxt.b[u / 4][1], u % 4, nxt.lo1[u / 4], nxt.hi1[u / 4]);
+      }
+      rescale_slot(q, false, c, cur.sg);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    wait_reads(nxt);
+#pragma unroll
+    for (int j = 0; j < (GROUP ? WN : 1); ++j) sg_last[j] = cur.sg[j];
+  };
+
   const int NS = (KB + KS - 1) / KS;  // steps per k group (a trailing one past K reads zeros)
 #pragma unroll
   for (int st = 0; st < kOwnRing; ++st)
@@ -436,13 +495,27 @@ __global__ __launch_bounds__(GM * GN * 64 * KS) void largem(const LargeMArgs a) 
 #pragma unroll
   for (int u = 0; u < kUnits; ++u) unpack0(o0, u);
   wait_reads(o0);
-  for (int i = 0; i < NS; i += kOwnRing) {
-    step(std::integral_constant<int, 0>{}, KS * i + wk, o0, o1, acc[0], acc[GROUP ? 1 : 0]);
-    if (i + 1 < NS) step(std::integral_constant<int, 1>{}, KS * (i + 1) + wk, o1, o0, acc[GROUP ? 1 : 0], acc[0]);
-    if (i + 2 < NS) step(std::integral_constant<int, 2>{}, KS * (i + 2) + wk, o0, o1, acc[0], acc[GROUP ? 1 : 0]);
-    if (i + 3 < NS) step(std::integral_constant<int, 3>{}, KS * (i + 3) + wk, o1, o0, acc[GROUP ? 1 : 0], acc[0]);
+  if constexpr (GROUP && kMfma >= 12) {
+#pragma unroll
+    for (int u = 0; u < kUnits; ++u) unpack_word(o0.b[u / 4][1], u % 4, o0.lo1[u / 4], o0.hi1[u / 4]);
+    for (int i = 0; i < NS; i += kOwnRing) {
+      step1(std::integral_constant<int, 0>{}, KS * i + wk, o0, o1, acc[0]);
+      if (i + 1 < NS) step1(std::integral_constant<int, 1>{}, KS * (i + 1) + wk, o1, o0, acc[0]);
+      if (i + 2 < NS) step1(std::integral_constant<int, 2>{}, KS * (i + 2) + wk, o0, o1, acc[0]);
+      if (i + 3 < NS) step1(std::integral_constant<int, 3>{}, KS * (i + 3) + wk, o1, o0, acc[0]);
+    }
+    // the last step's rescales that fall past its last slot
+#pragma unroll
+    for (int q = 0; q < kMfma; ++q) rescale_slot(q, true, acc[0], sg_last);
+  } else {
+    for (int i = 0; i < NS; i += kOwnRing) {
+      step(std::integral_constant<int, 0>{}, KS * i + wk, o0, o1, acc[0], acc[GROUP ? 1 : 0]);
+      if (i + 1 < NS) step(std::integral_constant<int, 1>{}, KS * (i + 1) + wk, o1, o0, acc[GROUP ? 1 : 0], acc[0]);
+      if (i + 2 < NS) step(std::integral_constant<int, 2>{}, KS * (i + 2) + wk, o0, o1, acc[0], acc[GROUP ? 1 : 0]);
+      if (i + 3 < NS) step(std::integral_constant<int, 3>{}, KS * (i + 3) + wk, o1, o0, acc[GROUP ? 1 : 0], acc[0]);
+    }
   }
-  if constexpr (GROUP) {
+  if constexpr (GROUP && kMfma < 12) {
     // the last step's partial sums (the set of step KB - 1)
     auto rescale_last = [&](v16i (&last)[WM][WN]) {
 #pragma unroll

@@ -22,6 +22,33 @@ def test_group_tile_edges(steps, M, N):
     check_all_outputs(x, W, s, group=True, rows=rows, label="group tile")
 
 
+# With at most one 128 x 128 tile per CU and a long K, the form that reads its
+# operands a step ahead: every remainder of its 4-deep ring.
+@pytest.mark.gpu
+@pytest.mark.parametrize("rest", [0, 1, 2, 3])
+def test_lone_group_tiles(rest):
+    from test_gpu_swiglu import check as check_gated
+    M, N, K = 1793, 2000, 8192 + 128 * rest
+    assert "largem<128x128,group,ahead>" in w.w4a8_linear_describe(M, N, K, w.SCALE_GROUP_F16)
+    x = I.activations(M, K, 880 + rest)
+    W, s = I.weights(N, K, 884 + rest, group=True)
+    rows = np.concatenate([np.arange(0, M, 120), np.arange(M - 10, M)])
+    check_all_outputs(x, W, s, group=True, rows=rows, label="lone group tile")
+    M, F, K = 201, 176, 2048 + 128 * rest
+    assert "largem<128x128,group,swiglu,ahead>" in w.w4a8_linear_swiglu_describe(M, 2 * F, K, w.SCALE_GROUP_F16)
+    check_gated(M, F, K, True, rest % 2 == 1, 888 + rest, "lone group tile")
+
+
+@pytest.mark.parametrize("M,N,K,form", [(1024, 4096, 8192, "group,ahead"), (1024, 4096, 8064, "group"), (1400, 4096, 8192, "group")])
+def test_lone_group_tile_choice(M, N, K, form):
+    assert f"largem<128x128,{form}>" in w.w4a8_linear_describe(M, N, K, w.SCALE_GROUP_F16)
+
+
+@pytest.mark.parametrize("M,F,K,form", [(1024, 2048, 2048, ",ahead"), (1024, 2048, 1920, ""), (1025, 2048, 2048, "")])
+def test_lone_gated_tile_choice(M, F, K, form):
+    assert f"largem<128x128,group,swiglu{form}>" in w.w4a8_linear_swiglu_describe(M, 2 * F, K, w.SCALE_GROUP_F16)
+
+
 @pytest.mark.parametrize("M,N,tile", [(768, 6144, 64), (1024, 6144, 128), (320, 24576, 64), (384, 24576, 128),
                                       (768, 4096, 64), (1024, 4096, 128), (256, 24576, 128), (192, 24576, 64)])
 def test_group_tile_choice(M, N, tile):
