@@ -108,7 +108,7 @@ def check_all_outputs(x_bits, W, s, *, group, codes=False, ref=None, rows=None, 
         ybf = (yb.astype(np.uint32) << 16).view(np.float32).astype(np.float64)
         err = np.abs(ybf - ref["y64"])
         bound = REL * np.abs(ref["y64"]) + GROUP_FLOOR * ref["bound"]
-        bad = err > bound
+        bad = ~(err <= bound)  # a NaN is outside it too
         assert not bad.any(), f"{label}: {bad.sum()} bf16 outputs outside tolerance, max err {err.max()}"
         err32 = np.abs(y32.astype(np.float64) - ref["y64"])
         assert np.all(err32 <= 1e-5 * np.abs(ref["y64"]) + GROUP_FLOOR * ref["bound"]), label
