@@ -42,6 +42,14 @@ __device__ __forceinline__ void lds_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
+// Keeps the LDS accesses on its two sides in program order: for data that
+// passes between the lanes of one wave, whose LDS accesses the hardware
+// serves in order.  No instruction.
+__device__ __forceinline__ void wave_order() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
+  __builtin_amdgcn_wave_barrier();
+}
+
 // MFMA operands from one packed 16-byte chunk: low nibbles (k .. k+15) and
 // high nibbles (k+16 .. k+31), each as 16 signed bytes of value 16 * w.
 __device__ __forceinline__ v4i nib_lo(uint4 c) {

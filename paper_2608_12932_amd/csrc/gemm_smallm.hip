@@ -338,18 +338,29 @@ __global__ __launch_bounds__(kThreads) void smallm(const SmallMArgs a) {
   // Lane (row r16, group g4) takes the
   // chunks 2 g4 and 2 g4 + 1 of its row.  Chunk c of row r lies at
   // c ^ ((r >> 1) & 7): 16 rows read at once fall on distinct banks.  LDS
-  // serves a wave in order, so neither a barrier nor a wait is needed.  With
-  // two column tiles or more the area is the wave's part of the reduction's.
+  // serves a wave in order, so neither a barrier nor a wait is needed, only
+  // that the compiler keeps a block's writes, its reads (of what other lanes
+  // wrote) and the next block's writes in this order: the reads' copy of the
+  // area's offset is opaque, so that it cannot tell their addresses from the
+  // writes', and both sides use one type.  Fences of the wave's scope, which
+  // also hold back every load between the stages, stand where the compiler
+  // otherwise moves so many that it spills registers (down M = 48 13.5 us a
+  // call without, 12.0 with); elsewhere they cost up to 6 %.
+  // With two column tiles or more the area is the wave's part of the
+  // reduction's.
+  constexpr bool kFenced = !SWIGLU && (EXACT || (MT == 2 && NT == 2));
   const uint8_t *xw_lo = nullptr, *xw_hi = nullptr;
   uint8_t *xw_wr = nullptr, *xw_wr8 = nullptr;
   if constexpr (XT) {
-    uint8_t* xw = l_body + (NT >= 2 ? wave * (MT * NT * kRedTile * 4)
-                                    : kWaves * MT * NT * kRedTile * 4 + wave * (MT * 2048));
+    const int xw = NT >= 2 ? wave * (MT * NT * kRedTile * 4)
+                           : kWaves * MT * NT * kRedTile * 4 + wave * (MT * 2048);
+    int xr = xw;
+    asm volatile("" : "+s"(xr));
     const int wr_row = lane >> 3, rsw = (r16 >> 1) & 7;
-    xw_wr = xw + wr_row * 128 + (((lane & 7) ^ (wr_row >> 1)) << 4);               // rows 0 - 7
-    xw_wr8 = xw + (8 + wr_row) * 128 + (((lane & 7) ^ (4 + (wr_row >> 1))) << 4);  // rows 8 - 15
-    xw_lo = xw + r16 * 128 + (((2 * g4) ^ rsw) << 4);
-    xw_hi = xw + r16 * 128 + (((2 * g4 + 1) ^ rsw) << 4);
+    xw_wr = l_body + xw + wr_row * 128 + (((lane & 7) ^ (wr_row >> 1)) << 4);               // rows 0 - 7
+    xw_wr8 = l_body + xw + (8 + wr_row) * 128 + (((lane & 7) ^ (4 + (wr_row >> 1))) << 4);  // rows 8 - 15
+    xw_lo = l_body + xr + r16 * 128 + (((2 * g4) ^ rsw) << 4);
+    xw_hi = l_body + xr + r16 * 128 + (((2 * g4 + 1) ^ rsw) << 4);
   }
 
   // ---- main loop
@@ -391,13 +402,13 @@ __global__ __launch_bounds__(kThreads) void smallm(const SmallMArgs a) {
       }
     } else {
 #pragma unroll
-      for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-        for (int e = 0; e < 2; ++e) *reinterpret_cast<uint4*>((e ? xw_wr8 : xw_wr) + mt * 2048) = ab[s][mt][e];
-#pragma unroll
       for (int mt = 0; mt < MT; ++mt) {
+        *reinterpret_cast<v4i*>(xw_wr + mt * 2048) = as_v4i(ab[s][mt][0]);
+        *reinterpret_cast<v4i*>(xw_wr8 + mt * 2048) = as_v4i(ab[s][mt][1]);
+        if constexpr (kFenced) wave_order();
         alo[mt] = *reinterpret_cast<const v4i*>(xw_lo + mt * 2048);
         ahi[mt] = *reinterpret_cast<const v4i*>(xw_hi + mt * 2048);
+        if constexpr (kFenced) wave_order();
       }
     }
 #pragma unroll
