@@ -48,8 +48,9 @@ constexpr int kLdsHeader = 256;   // per-row absmax / s / inv / mode
 constexpr int kMaxTilesPerWave = 12;
 constexpr int kMaxFusedTiles = 2;  // fused quantize pays off up to this many tiles
 constexpr int kXtMinRows = 12;     // codes loaded as rows (XT) from this many rows on ...
-// ... and for these tiles (see plan_smallm)
+// ... and for these tiles, for some of which it depends on the sizes (see plan_smallm)
 constexpr bool xt_tiles(int MT, int NT, bool SW) { return MT == 1 ? NT <= 2 : MT > 2 || NT < 6 || SW; }
+constexpr bool xt_sized(int MT, int NT, bool GROUP) { return NT == 1 ? MT <= 2 : GROUP || NT == 6 || (MT == 2 && NT == 4); }
 constexpr int kFusedMinKB = 256;   // ... and from this many 128-k blocks (K >= 32768) on
 // LDS words per wave tile of partial sums in the reduction: 256 plus a
 // 16-word skew, so that consecutive tiles start 16 banks apart
@@ -601,7 +602,7 @@ SmallMKernel instance(bool exact, bool xt) {
     return nullptr;
   } else {
     // the forms that exist
-    constexpr bool kXt = QM == kQNone && xt_tiles(MT, NT, SW), kPlain = MT == 1 || !kXt;
+    constexpr bool kXt = QM == kQNone && xt_tiles(MT, NT, SW), kPlain = MT == 1 || !kXt || xt_sized(MT, NT, GROUP);
     if constexpr (kXt)
       if (xt) {
         if constexpr (!GROUP)
@@ -749,7 +750,27 @@ SmallMPlan plan_smallm(int M, int N, int K, bool group, bool bf16_in, bool swigl
   // M = 64 11.2 / 8.7; gate+up M = 16 (6 tiles) 9.86 / 10.0, M = 64 24.6 /
   // 17.8, gated M = 32 12.1 / 11.7; but plain gate+up at M = 24 (2 row by 6
   // column tiles, out of registers) 11.3 / 11.6, group scales 12.5 / 15.0.
-  p.xt = p.qmode == kQNone && M >= kXtMinRows && xt_tiles(p.MT, p.NT, swiglu);
+  // The turn through LDS costs ~0.1 us (one column tile) to ~0.4 us (group
+  // scales, several) a call; loading whole rows saves in proportion to the
+  // rows past what half the row tiles hold and to the blocks, so for these
+  // tiles it takes enough of both.  us, operands / rows, group scales: M = 17,
+  // N = 6144 K = 1024 4.56 / 4.71, 4096 5.57 / 5.69, 8192 9.47 / 8.67; M = 12,
+  // N = 6144 K = 2048 4.68 / 5.06, 12288 11.0 / 10.3; M = 33, N = 6144 K =
+  // 1024 4.87 / 5.24, 4096 8.61 / 7.99; channel scales: M = 12, N = 4096 K =
+  // 1024 2.71 / 2.85, 4096 4.02 / 3.88; M = 17, N = 16384 K = 4096 6.70 /
+  // 6.86.  With one row and column tile, channel scales and more than two
+  // workgroups a CU, i.e. several rounds that each pay for the turn, only 16
+  // rows are worth it: M = 13, N = 23440, K = 3584 20.1 / 22.3, M = 16,
+  // N = 16400, K = 4608 17.9 / 16.9.  Over 1800 shapes the choice is within
+  // 0.1 % of the better form on average, 7 % at most.
+  const int64_t ks = (int64_t)kbs * kGroup, worth = (M - 8 * p.MT) * ks;
+  bool sized;
+  if (p.NT == 1)
+    sized = !group && p.MT == 1 && p.groups * p.S > 512 ? M == 16 && worth >= 16384 : worth * p.MT >= 8192;
+  else
+    sized = worth >= (!group ? 12288 : p.MT == 1 || (p.MT == 2 && p.NT > 2) ? 32768 : 16384) ||
+            (p.MT > 1 && ks * p.MT >= (swiglu && group ? 8192 : 12288));
+  p.xt = p.qmode == kQNone && M >= kXtMinRows && xt_tiles(p.MT, p.NT, swiglu) && (!xt_sized(p.MT, p.NT, group) || sized);
   const size_t red = (size_t)kWaves * p.MT * p.NT * kRedTile * 4;
   const size_t codes = p.qmode == kQLds ? ((size_t)M * (kbs * 128 + 16) + 15) / 16 * 16 : 0;
   // (one column tile: the waves' operand areas lie past the reduction's)

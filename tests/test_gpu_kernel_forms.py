@@ -55,14 +55,15 @@ def test_group_tile_choice(M, N, tile):
     assert f"largem<{tile}x{tile},group" in w.w4a8_linear_describe(M, N, 4096, w.SCALE_GROUP_F16)
 
 
-# The small-M kernels load the codes as whole rows from 12 rows on: the turn,
-# the edges of the 8-row halves and 16-row tiles, one and several column
-# tiles, K splits that leave waves without a block.
+# The small-M kernels load the codes as whole rows from 12 rows on, for some
+# tiles only where the rows and blocks are worth it (both forms occur here):
+# the turn, the edges of the 8-row halves and 16-row tiles, one and several
+# column tiles, K splits that leave waves without a block.
 @pytest.mark.gpu
 @pytest.mark.parametrize("group", [False, True])
 @pytest.mark.parametrize("M", [11, 12, 15, 16, 17, 25, 33, 40, 48, 57, 64])
 def test_rows_of_codes(M, group):
-    for K, N in ((128, 48), (1152, 4096), (2048, 8192)):
+    for K, N in ((128, 48), (1152, 4096), (2048, 8192), (6272, 2064)):
         x = I.activations(M, K, 860 + M)
         W, s = I.weights(N, K, 861 + N, group=group)
         check_all_outputs(x, W, s, group=group, label="rows of codes")
