@@ -1,11 +1,12 @@
 """MI355X (gfx950) W4A8 linear layer: Python binding of libw4a8.so.
 
 The functions carry the names of the C ABI in include/w4a8.h and only
-marshal arguments (the plain case of the hot ones in csrc/binding.cpp): they check dtypes and shapes of torch tensors, allocate
-outputs with torch (device memory is the one thing torch is used for here),
-and pass raw pointers plus torch's current HIP stream to the library.  Every
-step of the computation runs in the HIP kernels; there is no fallback, and
-loading fails loudly when the library has not been built.
+marshal arguments (the plain case of the hot ones in csrc/binding.cpp): they
+check dtypes and shapes of torch tensors, allocate outputs with torch (device
+memory is the one thing torch is used for here), and pass raw pointers plus
+torch's current HIP stream to the library.  Every step of the computation runs
+in the HIP kernels; there is no fallback, and loading fails loudly when the
+libraries have not been built.
 """
 from __future__ import annotations
 
@@ -17,6 +18,7 @@ import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libw4a8.so")
+NATIVE_PATH = os.path.join(_HERE, "_native.so")
 
 W4A8_OK, W4A8_EINVAL, W4A8_EUNSUPPORTED, W4A8_ERANGE, W4A8_EHIP = 0, 1, 2, 3, 4
 SCALE_CHANNEL_F32, SCALE_GROUP_F16 = 0, 1
@@ -46,11 +48,16 @@ _fast = None
 
 
 def _load_fast():
-    """The native fast path of the hot calls (csrc/binding.cpp)."""
+    """The native fast path of the hot calls (csrc/binding.cpp), raises if it
+    has not been built or does not fit libw4a8.so, this Python or this torch."""
     global _fast
     if _fast is None:
         lib()
-        from . import _native
+        try:
+            from . import _native
+        except ImportError as e:
+            raise RuntimeError(f"{NATIVE_PATH} is missing or does not load ({e}): build it with "
+                               "__graft_entry__.build() before using the W4A8 kernels") from e
 
         _fast = _native
     return _fast

@@ -132,6 +132,16 @@ def test_malformed_calls_are_rejected_without_launch():
     assert L.w4a8_pack_weights(None, 256, 256, fake, None) == w.W4A8_EINVAL
 
 
+def test_missing_native_module_says_what_to_build(monkeypatch):
+    # (None in sys.modules makes the import fail as a missing file does)
+    import sys
+    monkeypatch.setattr(w, "_fast", None)
+    monkeypatch.setitem(sys.modules, "paper_2608_12932_amd._native", None)
+    monkeypatch.delattr(w, "_native", raising=False)
+    with pytest.raises(RuntimeError, match="_native.so.*build"):
+        w._load_fast()
+
+
 def test_swiglu_plans_and_rejections():
     # gate+up verify: the same column groups as the plain projection, gate
     # and up tiles paired (NT even)
