@@ -261,7 +261,16 @@ class Workspace:
     def __init__(self, device="cuda"):
         self.device = torch.device(device)
         self.buf = torch.zeros(0, dtype=torch.uint8, device=self.device)
-        self._home = (self.buf, None)  # the buffer and the stream that its memory is ordered on (None: empty)
+        self._home = (self.buf, None)  # the buffer and the stream that its memory is ordered on (None: empty or not known)
+
+    def __getstate__(self):
+        """Copies and pickles hold the device and the buffer: on which stream
+        the new buffer's memory is ordered is not known to them."""
+        return {"device": self.device, "buf": self.buf}
+
+    def __setstate__(self, state):
+        self.device, self.buf = state["device"], state["buf"]
+        self._home = (self.buf, None)
 
     def get(self, nbytes: int, stream: torch.cuda.Stream | None = None) -> torch.Tensor:
         s = _torch_stream(stream, self.device)

@@ -48,7 +48,8 @@ w4a8_status without_gil(F f) {  // launches may wait for room in the queue
 // linear(swiglu, x, w_packed, w_scale, N, x_scale, scale_mode, out_kind, out,
 //        workspace, workspace_stream, is_workspace)
 // workspace_stream: the stream that a Workspace's buffer (is_workspace)
-// belongs to, None while it is empty.  A negative int is the size that an
+// belongs to, None while it is empty or that is not known (a copy's).  A
+// negative int is the size that an
 // otherwise plain call's Workspace has to grow to.
 PyObject* linear(PyObject*, PyObject* const* a, Py_ssize_t n) {
   HANDLE_TH_ERRORS

@@ -142,6 +142,21 @@ def test_missing_native_module_says_what_to_build(monkeypatch):
         w._load_fast()
 
 
+def test_workspace_copies_know_no_stream():
+    import copy
+    import pickle
+    import torch
+    ws = w.Workspace("cpu")
+    ws.buf = torch.zeros(64, dtype=torch.uint8)
+    ws._home = (ws.buf, 7)  # as a call on stream 7 leaves it
+    for c in (copy.copy(ws), copy.deepcopy(ws), pickle.loads(pickle.dumps(ws))):
+        assert c.device == ws.device and c.buf.numel() == 64
+        assert c._home[0] is c.buf and c._home[1] is None
+    old = w.Workspace.__new__(w.Workspace)  # a pickle from before the home was kept
+    old.__setstate__({"device": ws.device, "buf": ws.buf})
+    assert old._home[1] is None
+
+
 def test_swiglu_plans_and_rejections():
     # gate+up verify: the same column groups as the plain projection, gate
     # and up tiles paired (NT even)
