@@ -36,13 +36,16 @@ int64_t as_int(PyObject* o) { return PyLong_AsLongLong(o); }  // -1 with an erro
 
 hipStream_t current_stream() { return c10::hip::getCurrentHIPStream().stream(); }
 
+// Runs f without the interpreter's lock, also where it throws: launches may
+// wait for room in the queue, allocations for the allocator's lock, whose
+// holder may itself be waiting for the interpreter's.
 template <class F>
-w4a8_status without_gil(F f) {  // launches may wait for room in the queue
-  w4a8_status s;
-  Py_BEGIN_ALLOW_THREADS
-  s = f();
-  Py_END_ALLOW_THREADS
-  return s;
+w4a8_status without_gil(F f) {
+  struct Released {
+    PyThreadState* state = PyEval_SaveThread();
+    ~Released() { PyEval_RestoreThread(state); }
+  } released;
+  return f();
 }
 
 // linear(swiglu, x, w_packed, w_scale, N, x_scale, scale_mode, out_kind, out,
@@ -97,24 +100,22 @@ PyObject* linear(PyObject*, PyObject* const* a, Py_ssize_t n) {
     wk_bytes = (size_t)buf->numel();
   }
 
-  at::Tensor y;
-  if (a[8] == Py_None) {
-    y = at::empty({M, cols}, x->options().dtype(out_type));
-  } else {
-    const at::Tensor* out = plain(a[8], out_type);
+  const at::Tensor* out = nullptr;
+  if (a[8] != Py_None) {
+    out = plain(a[8], out_type);
     if (!out || out->dim() != 2 || out->size(0) != M || out->size(1) != cols) Py_RETURN_NONE;
-    y = *out;
   }
   const void *xp = x->data_ptr(), *sp = ws ? ws->data_ptr() : nullptr;
   const float* xsp = xs ? static_cast<const float*>(xs->data_ptr()) : nullptr;
   const uint8_t* wpp = static_cast<const uint8_t*>(wp->data_ptr());
-  void* yp = y.data_ptr();
+  at::Tensor y;
   const w4a8_status s = without_gil([&] {
-    return (swiglu ? w4a8_linear_swiglu : w4a8_linear)(xp, in_kind, xsp, M, K, wpp, sp, (int)mode, N, yp, (int)kind, wk,
-                                                       wk_bytes, stream);
+    y = out ? *out : at::empty({M, cols}, x->options().dtype(out_type));
+    return (swiglu ? w4a8_linear_swiglu : w4a8_linear)(xp, in_kind, xsp, M, K, wpp, sp, (int)mode, N, y.data_ptr(), (int)kind,
+                                                       wk, wk_bytes, stream);
   });
   if (s != W4A8_OK) return PyLong_FromLong(s);
-  if (a[8] != Py_None) return Py_NewRef(a[8]);
+  if (out) return Py_NewRef(a[8]);
   return THPVariable_Wrap(std::move(y));
   END_HANDLE_TH_ERRORS
 }
@@ -140,12 +141,14 @@ PyObject* quantize(PyObject*, PyObject* const* a, Py_ssize_t n) {
     if (!g || g->dim() != 1 || g->size(0) != K || !PyFloat_CheckExact(a[2])) Py_RETURN_NONE;
     eps = (float)PyFloat_AS_DOUBLE(a[2]);
   }
-  at::Tensor q = at::empty({M, K}, x->options().dtype(at::kChar)), s = at::empty({M}, x->options().dtype(at::kFloat));
+  at::Tensor q, s;
   const uint16_t *xp = static_cast<const uint16_t*>(x->data_ptr()), *gp = g ? static_cast<const uint16_t*>(g->data_ptr()) : nullptr;
-  int8_t* qp = static_cast<int8_t*>(q.data_ptr());
-  float* sp = static_cast<float*>(s.data_ptr());
   const hipStream_t stream = current_stream();
   const w4a8_status st = without_gil([&] {
+    q = at::empty({M, K}, x->options().dtype(at::kChar));
+    s = at::empty({M}, x->options().dtype(at::kFloat));
+    int8_t* qp = static_cast<int8_t*>(q.data_ptr());
+    float* sp = static_cast<float*>(s.data_ptr());
     return g ? w4a8_rmsnorm_quantize_act(xp, gp, eps, M, K, qp, sp, stream) : w4a8_quantize_act(xp, M, K, qp, sp, stream);
   });
   if (st != W4A8_OK) return PyLong_FromLong(st);
@@ -173,14 +176,16 @@ PyObject* flow_step(PyObject*, PyObject* const* a, Py_ssize_t n) {
   }
   const bool stats = a[4] == Py_True;
   at::Tensor st;
-  if (stats) st = at::empty({B, 4}, x->options().dtype(at::kDouble));
   float* xp = static_cast<float*>(x->data_ptr());
   const uint16_t* vp = v ? static_cast<const uint16_t*>(v->data_ptr()) : nullptr;
   uint16_t* cp = static_cast<uint16_t*>(c->data_ptr());
-  double* stp = stats ? static_cast<double*>(st.data_ptr()) : nullptr;
   const float dt = (float)PyFloat_AS_DOUBLE(a[3]);
   const hipStream_t stream = current_stream();
-  const w4a8_status s = without_gil([&] { return w4a8_flow_step(xp, vp, cp, B, len, dt, repeat, stp, stream); });
+  const w4a8_status s = without_gil([&] {
+    if (stats) st = at::empty({B, 4}, x->options().dtype(at::kDouble));
+    double* stp = stats ? static_cast<double*>(st.data_ptr()) : nullptr;
+    return w4a8_flow_step(xp, vp, cp, B, len, dt, repeat, stp, stream);
+  });
   if (s != W4A8_OK) return PyLong_FromLong(s);
   if (!stats) Py_RETURN_TRUE;
   return THPVariable_Wrap(std::move(st));
