@@ -80,6 +80,12 @@ PyObject* linear(PyObject*, PyObject* const* a, Py_ssize_t n) {
   const int64_t M = x->size(0), K = x->size(1), cols = swiglu ? N / 2 : N;
   const at::ScalarType out_type = kind == W4A8_OUT_BF16 ? at::kBFloat16 : kind == W4A8_OUT_F32 ? at::kFloat : at::kInt;
 
+  const at::Tensor* out = nullptr;
+  if (a[8] != Py_None) {
+    out = plain(a[8], out_type);
+    if (!out || out->dim() != 2 || out->size(0) != M || out->size(1) != cols) Py_RETURN_NONE;
+  }
+
   const size_t need = swiglu ? w4a8_linear_swiglu_workspace_bytes(M, N, K, (int)mode, in_kind)
                              : w4a8_linear_workspace_bytes(M, N, K, (int)mode, in_kind);
   const hipStream_t stream = current_stream();
@@ -100,11 +106,6 @@ PyObject* linear(PyObject*, PyObject* const* a, Py_ssize_t n) {
     wk_bytes = (size_t)buf->numel();
   }
 
-  const at::Tensor* out = nullptr;
-  if (a[8] != Py_None) {
-    out = plain(a[8], out_type);
-    if (!out || out->dim() != 2 || out->size(0) != M || out->size(1) != cols) Py_RETURN_NONE;
-  }
   const void *xp = x->data_ptr(), *sp = ws ? ws->data_ptr() : nullptr;
   const float* xsp = xs ? static_cast<const float*>(xs->data_ptr()) : nullptr;
   const uint8_t* wpp = static_cast<const uint8_t*>(wp->data_ptr());

@@ -109,3 +109,17 @@ def test_refused_calls():
         w.w4a8_rmsnorm_quantize_act(x, torch.ones(K + 8, dtype=torch.bfloat16, device=dev()), 1e-6)
     with pytest.raises(ValueError):
         w.w4a8_flow_step(torch.zeros(2, 8, device=dev()), None, torch.zeros(2, 4, dtype=torch.bfloat16, device=dev()), 0.1)
+
+
+def test_refused_calls_leave_the_workspace_alone():
+    K, N, M = 512, 64, 20
+    x = bf16_dev(I.activations(M, K, 912))
+    W, s = I.weights(N, K, 913)
+    wp, sd = pack(W), scales_dev(s)
+    ws = w.Workspace()
+    for bad in (dict(x=x.float()), dict(x=x[:, ::2]), dict(wp=wp.cpu()), dict(sd=sd.half()),
+                dict(out=torch.empty(M, N + 1, dtype=torch.bfloat16, device=dev()))):
+        a = dict(x=x, wp=wp, sd=sd, out=None) | bad
+        with pytest.raises((TypeError, ValueError)):
+            w.w4a8_linear(a["x"], a["wp"], a["sd"], N, out=a["out"], workspace=ws)
+        assert ws.buf.numel() == 0, list(bad)
