@@ -306,8 +306,8 @@ def _workspace_ptr(workspace, need: int, device, stream):
 
 def _linear_fast(swiglu: int, x, w_packed, w_scale, N, x_scale, scale_mode, out_kind, out, workspace):
     """The native path of both linear calls on the current stream; None where
-    it does not take the call (a Workspace that has to grow or that belongs
-    to another stream, arguments that need an error, ...)."""
+    it does not take the call (a Workspace that belongs to another stream,
+    arguments that need an error, ...)."""
     buf, home, own = workspace, None, False
     if type(workspace) is Workspace:
         own = True

@@ -16,6 +16,7 @@
 
 #include <ATen/core/Tensor.h>
 #include <ATen/ops/empty.h>
+#include <ATen/ops/zeros.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
@@ -91,7 +92,8 @@ PyObject* linear(PyObject*, PyObject* const* a, Py_ssize_t n) {
   const hipStream_t stream = current_stream();
   void* wk = nullptr;
   size_t wk_bytes = 0;
-  if (need) {
+  const bool temporary = need && a[9] == Py_None && a[11] != Py_True;
+  if (need && !temporary) {
     const at::Tensor* buf = plain(a[9], at::kByte);
     if (!buf) Py_RETURN_NONE;
     if (a[11] == Py_True) {  // a Workspace: of this stream (its memory is ordered on it), and large enough
@@ -112,6 +114,12 @@ PyObject* linear(PyObject*, PyObject* const* a, Py_ssize_t n) {
   at::Tensor y;
   const w4a8_status s = without_gil([&] {
     y = out ? *out : at::empty({M, cols}, x->options().dtype(out_type));
+    at::Tensor tmp;  // released to the allocator on this stream, which orders its next use
+    if (temporary) {
+      tmp = at::zeros({(int64_t)need}, x->options().dtype(at::kByte));
+      wk = tmp.data_ptr();
+      wk_bytes = need;
+    }
     return (swiglu ? w4a8_linear_swiglu : w4a8_linear)(xp, in_kind, xsp, M, K, wpp, sp, (int)mode, N, y.data_ptr(), (int)kind,
                                                        wk, wk_bytes, stream);
   });
