@@ -12,6 +12,26 @@ from helpers import bf16_dev, dev, pack, scales_dev
 pytestmark = pytest.mark.gpu
 
 
+class Record:
+    """The native module with the results of its calls (None: declined)."""
+
+    def __init__(self, monkeypatch):
+        self.native, self.got = w._load_fast(), []
+        monkeypatch.setattr(w, "_fast", self)
+
+    def __getattr__(self, name):
+        def call(*args):
+            self.got.append(getattr(self.native, name)(*args))
+            return self.got[-1]
+        return call
+
+    def last(self, f, *args, **kw):
+        """f's result and what the last native call of it gave."""
+        self.got.clear()
+        r = f(*args, **kw)
+        return r, self.got[-1]
+
+
 def same(a, b):
     assert a.dtype == b.dtype and a.shape == b.shape
     assert torch.equal(a.contiguous().view(torch.uint8), b.contiguous().view(torch.uint8))
@@ -109,6 +129,65 @@ def test_refused_calls():
         w.w4a8_rmsnorm_quantize_act(x, torch.ones(K + 8, dtype=torch.bfloat16, device=dev()), 1e-6)
     with pytest.raises(ValueError):
         w.w4a8_flow_step(torch.zeros(2, 8, device=dev()), None, torch.zeros(2, 4, dtype=torch.bfloat16, device=dev()), 0.1)
+
+
+def test_native_path_is_taken(monkeypatch):
+    K, N, M = 512, 64, 20
+    rec = Record(monkeypatch)
+    x = bf16_dev(I.activations(M, K, 910))
+    (q, sx), got = rec.last(w.w4a8_quantize_act, x)
+    assert type(got) is tuple and got[0] is q
+    r, got = rec.last(w.w4a8_rmsnorm_quantize_act, x, torch.ones(K, dtype=torch.bfloat16, device=dev()), 1e-6)
+    assert r is got
+    for f, group in ((w.w4a8_linear, False), (w.w4a8_linear, True), (w.w4a8_linear_swiglu, True)):
+        W, s = I.weights(N, K, 911, group=group)
+        wp, sd = pack(W), scales_dev(s)
+        kw = dict(scale_mode=w.SCALE_GROUP_F16 if group else w.SCALE_CHANNEL_F32)
+        ws = w.Workspace()
+        need = w.w4a8_linear_workspace_bytes(M, N, K, int(group))
+        assert need > 0 and w.w4a8_linear_workspace_bytes(M, N, K, int(group), w.IN_I8) == 0
+        for wk in (ws, ws, None, torch.zeros(need, dtype=torch.uint8, device=dev())):
+            y, got = rec.last(f, x, wp, sd, N, workspace=wk, **kw)
+            assert y is got
+        y, got = rec.last(f, q, wp, sd, N, x_scale=sx, **kw)
+        assert y is got
+        out = torch.empty_like(y)
+        y, got = rec.last(f, x, wp, sd, N, workspace=ws, out=out, **kw)
+        assert y is out and got is out
+    f = lambda v, stats: rec.last(w.w4a8_flow_step, torch.zeros(2, 8, device=dev()), v,
+                                  torch.zeros(2, 8, dtype=torch.bfloat16, device=dev()), 0.1, stats=stats)
+    v = torch.ones(2, 8, dtype=torch.bfloat16, device=dev())
+    st, got = f(v, True)
+    assert st is got and st.shape == (2, 4)
+    assert f(v, False) == (None, True) and f(None, False) == (None, True)
+
+
+def test_native_path_declines(monkeypatch):
+    import copy
+    K, N, M = 512, 64, 20
+    rec = Record(monkeypatch)
+    x = bf16_dev(I.activations(M, K, 912))
+    W, s = I.weights(N, K, 913)
+    wp, sd, ws = pack(W), scales_dev(s), w.Workspace()
+    ref = w.w4a8_linear(x, wp, sd, N, workspace=ws)
+    torch.cuda.synchronize()
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):  # a Workspace of another stream, a copy of one
+        y, got = rec.last(w.w4a8_linear, x, wp, sd, N, workspace=ws)
+        twin = copy.deepcopy(ws)
+    assert got is None
+    side.synchronize()
+    same(y, ref)
+    y, got = rec.last(w.w4a8_linear, x, wp, sd, N, workspace=twin)
+    assert got is None
+    same(y, ref)
+
+    class Sub(torch.Tensor):
+        pass
+
+    y, got = rec.last(w.w4a8_linear, x.as_subclass(Sub), wp, sd, N)
+    assert got is None
+    same(y.as_subclass(torch.Tensor), ref)
 
 
 def test_refused_calls_leave_the_workspace_alone():
