@@ -35,7 +35,7 @@ LargeMPlan plan_largem(int M, int N, int K, bool group, bool swiglu) {
   p.group = group;
   p.swiglu = swiglu;
   double best = -1.0;
-  for (int c = 0; c < kMenuSize; ++c) {
+  for (int c = 0; c < kMenuSize && (!group || swiglu); ++c) {  // plain group scales choose below
     const TileCfg& t = kMenu[c];
     if (group && !t.group_ok) continue;
     if (t.ks > 1) continue;  // the k-split form replaces entry 2 below
@@ -65,7 +65,9 @@ LargeMPlan plan_largem(int M, int N, int K, bool group, bool swiglu) {
   // N = 1536 .. 24576; at the turns, 128 x 128 against 64 x 64 in us:
   // qkv M = 768 34.3 / 30.4 (2 tiles a CU against 5), M = 1024 34.1 / 39.5
   // (2, 6); gate+up M = 320 50.8 / 47.7 (3, 8), M = 384 51.0 / 54.2 (3, 9);
-  // o M = 768 23.6 / 20.6 (1, 3), M = 1024 24.1 / 28.1 (1, 4).
+  // o M = 768 23.6 / 20.6 (1, 3), M = 1024 24.1 / 28.1 (1, 4).  Both sides
+  // scale with K alike: N = 4096, K = 1024 M = 512 8.9 / 6.3, M = 777 9.4 /
+  // 10.3, K = 12288 M = 512 62.8 / 42.4, M = 777 60.7 / 77.4.
   if (group && !swiglu) {
     auto tiles_of = [&](int B) { return (int64_t)((M + B - 1) / B) * ((N + B - 1) / B); };
     auto cost = [](int64_t tiles, double lone, double each) {

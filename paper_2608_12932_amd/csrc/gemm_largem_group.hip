@@ -27,10 +27,10 @@ namespace {
 // loads, waits and scalar instructions and waits out every latency: with the
 // template's 296 registers (one workgroup per CU) a step took ~1430 cycles.
 // Two workgroups per CU, which pass their barriers, prologues and epilogues
-// independently, fill each other's gaps.  So registers are held to 256: one
-// operand set, read after the barrier instead of a step ahead, partial sums
-// of two 32 x 32 blocks, no scales kept.  The stage ring is 3 deep: two
-// stages of loads in flight under a step.
+// independently, fill each other's gaps.  So registers are held to 256 (196
+// are used): one operand set, read after the barrier instead of a step
+// ahead, partial sums of two 32 x 32 blocks, no scales kept.  The stage ring
+// is 3 deep: two stages of loads in flight under a step.
 template <bool SW>
 __global__ __launch_bounds__(256, 2) void largem_group128(const LargeMArgs a) {
   constexpr int kRing = kGroup128Ring, BM = 128, BN = 128, kThreads = 256;

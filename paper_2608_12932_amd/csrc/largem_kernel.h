@@ -59,13 +59,12 @@ namespace {
 struct TileCfg {
   int WM, WN, GM, GN, ring;
   int ks;          // k groups of GM x GN waves (each with ring / ks stages)
-  double quality;  // relative efficiency of the tile shape (operand reuse)
+  double quality;  // relative efficiency of the tile shape (operand reuse); not asked for plain group scales
   bool group_ok;   // fits the registers with group-mode accumulators
   bool plain_ok;   // serves the plain output (its fp32 tile fits the LDS ring)
   bool gated_ok;   // serves the gated output (an even number of blocks per wave)
 };
-// The weights come from plan sweeps of the layer shapes at M = 256..2048 in
-// both scale modes.  A 64 x 96 tile (two waves) lost to 64 x 64 wherever it
+// The weights come from plan sweeps of the layer shapes at M = 256..2048.  A 64 x 96 tile (two waves) lost to 64 x 64 wherever it
 // was chosen (group qkv at M = 256: 23.4 against 16.4 us) and was dropped.
 // 128 x 256 serves only the gated output: its plain fp32 tile (133 KB)
 // would not fit the 128 KB ring, the gated one (64 KB) does.
