@@ -298,3 +298,23 @@ def test_positions_at_the_type_limits():
     o = run(q, k, v, np.full(Nq, last, np.int32), pos_k, cos_t, sin_t, float(scale))
     o64, bnd = oracle.streaming_attention(q, k, v, np.full(Nq, 63), np.maximum(pos_k, 0), cos_t, sin_t, scale)
     assert (np.abs(o - o64) <= 2.0 ** -8 * np.abs(o64) + 2.0 ** -8 * bnd + 1e-30).all()
+
+
+def test_repeated_calls_agree():
+    # every sum runs in a fixed order: the same bits from call to call, also
+    # with other work between the calls
+    for V, F, T, H, Hkv in ((4, 4, 192, 32, 8), (2, 3, 40, 8, 2), (1, 3, 33, 28, 4)):
+        pos_k, pos_q = window(V, F, T, 1)
+        Nq, Nk = len(pos_q), len(pos_k)
+        print(f"[case] repeated calls {V}x{F}x{T}", flush=True)
+        bf = lambda n, s: torch.from_numpy(I.activations(n, D, s).view(np.int16)).to(dev()).view(torch.bfloat16)
+        q, k, v = bf(H * Nq, 870).view(H, Nq, D), bf(Hkv * Nk, 871).view(Hkv, Nk, D), bf(Hkv * Nk, 872).view(Hkv, Nk, D)
+        pq, pk = (torch.from_numpy(p).to(dev()) for p in (pos_q, pos_k))
+        cos_t, sin_t = (torch.from_numpy(a).to(dev()) for a in oracle.rope_tables(Nk, D, base=1e6))
+        call = lambda: w.w4a8_stream_attention(q, k, v, pq, pk, cos_t, sin_t, D ** -0.5)
+        first = call()
+        for i in range(30):
+            again = call()
+            if i % 3 == 0:
+                again.clone().float().square_()
+            assert torch.equal(again.view(torch.int16), first.view(torch.int16)), i
