@@ -274,9 +274,11 @@ static_assert(kMaxSkipTiles <= 512, "a list entry holds 9 bits of tile number");
 // value fragment read from LDS feeds 32 queries, the tiles go from memory
 // straight into the LDS stage (no registers), and the softmax rescales
 // only where a maximum moves (below).  The 4 x 4 x 192 window with 32 heads took
-// 65.7 us with 16 queries a wave and values transposed through registers,
-// 50.6 us so.  (Two heads of a kv head per workgroup of 8 waves halve the
-// fill and took 43 us: one workgroup per CU, whose waves all wait at once.)
+// 65.7 us with 16 queries a wave and values transposed through registers and
+// 50.6 us so, in two key splits with a merge of 5.1 us; 49.8 us with the
+// queries rotated once a workgroup, without splits.  (Two heads of a kv head
+// per workgroup of 8 waves halve the fill and took 43 us: one workgroup per
+// CU, whose waves all wait at once.)
 // Rows are swizzled by the fetching lanes:
 //   keys    16-byte chunk c of key j at c ^ (j & 15): the 16 keys that an
 //           operand read touches at once lie on 16 distinct chunks;
